@@ -1,5 +1,6 @@
 // Fused dequantisation + single-query decode attention (Eq. lattn over the
-// decoded cache of Sec. 3.1), general kernels for every supported shape.
+// decoded cache of Sec. 3.1), general kernels for every supported shape, and
+// the choice between them and the matrix-core kernels.
 //
 // Three launches on the caller's stream:
 //   prep : q~_h = Pi q_h per (group, head); when the table fits (<= 64 KB per
@@ -65,27 +66,30 @@ static AttnPlan make_plan(int64_t n_groups, int G, int64_t T, const Shape& s) {
   return p;
 }
 
+// Whether a call takes the matrix-core kernel of attn_k4.hip.  Codes that it
+// reads with run-time index widths may need more workspace there than in the
+// general kernels (8 heads' records whatever G): they stay here where that
+// would no longer fit the static scratch.
+static bool use_k4(int64_t n_groups, int G, int64_t T, const Shape& s) {
+  if (!attn_k4_applies(G, s) || !attn_k4_fits(n_groups, T)) return false;
+  const size_t need = attn_k4_workspace_bytes(n_groups, T, s);
+  return need <= FIBQ_ATTN_SCRATCH_BYTES || need <= make_plan(n_groups, G, T, s).total ||
+         s.k == 2 || (s.k == 4 && (s.w == 8 || s.w == 12)) || (s.k == 8 && s.w == 6 && G == 8);
+}
+
 size_t attn_workspace_bytes(int64_t n_groups, int G, int64_t T, Shape s) {
   size_t b = make_plan(n_groups, G, T, s).total;
-  if (attn_fast_applies(G, s)) {
-    const size_t f = attn_fast_workspace_bytes(n_groups, T);
-    if (f > b) b = f;
-  }
   if (attn_w4_applies(G, s)) {
     const size_t f = attn_w4_workspace_bytes(n_groups, T);
     if (f > b) b = f;
   }
-  if (attn_k4_applies(G, s)) {
+  if (use_k4(n_groups, G, T, s)) {
     const size_t f = attn_k4_workspace_bytes(n_groups, T, s);
     if (f > b) b = f;
   }
   return b;
 }
 
-int launch_attn_fast(const void* q, int q_dtype, const uint8_t* kp, const uint16_t* kn,
-                     const uint8_t* vp, const uint16_t* vn, int64_t n_groups, int64_t T,
-                     int64_t T_stride, const Shape& s, const float* R, const float* C,
-                     float scale, float* out, void* ws, hipStream_t st);
 int launch_attn_k4(const void* q, int q_dtype, const uint8_t* kp, const uint16_t* kn,
                    const uint8_t* vp, const uint16_t* vn, int64_t n_groups, int G, int64_t T,
                    int64_t T_stride, const Shape& s, const float* R, const float* C, float scale,
@@ -391,25 +395,23 @@ int launch_attn(const void* q, int q_dtype, const uint8_t* kp, const uint16_t* k
                 float* out, void* ws, size_t ws_bytes, void* stream) {
   (void)ws_bytes;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // matrix-core kernel for the sub-one-bit shapes; its payload loads need
-  // 4-byte (P = 4) or 2-byte (P = 6) aligned payload pointers
-  const uintptr_t align = (s.w == 4) ? 3u : 1u;
-  if (attn_w4_applies(G, s) && T < (1LL << 30) &&
-      ((reinterpret_cast<uintptr_t>(kn) | reinterpret_cast<uintptr_t>(vn)) & 1u) == 0)
+  const bool norms2 =
+      ((reinterpret_cast<uintptr_t>(kn) | reinterpret_cast<uintptr_t>(vn)) & 1u) == 0;
+  // The 4-bit shape's own kernel where the groups are many: its one block per
+  // group merges up to 256 / n_groups records (1 group of 131072 tokens 84 us,
+  // 32 in attn_k4; 32 groups of 8192: 16.1 against 18.0).
+  if (attn_w4_applies(G, s) && n_groups >= 16 && T < (1LL << 30) && norms2)
     return launch_attn_w4(q, q_dtype, kp, kn, vp, vn, n_groups, T, T_stride, R, C, scale, out, ws,
                           st);
-  if (attn_fast_applies(G, s) && T < (1LL << 30) &&  // 32-bit token indices
-      ((reinterpret_cast<uintptr_t>(kp) | reinterpret_cast<uintptr_t>(vp)) & align) == 0 &&
-      ((reinterpret_cast<uintptr_t>(kn) | reinterpret_cast<uintptr_t>(vn)) & 1u) == 0)
-    return launch_attn_fast(q, q_dtype, kp, kn, vp, vn, n_groups, T, T_stride, s, R, C, scale, out,
-                            ws, st);
-  // matrix-core kernel for k = 4 (and k = 2, w = 4 or 6, read as pairs of
-  // blocks); payload quarters are read as dwords or 16-bit halves
-  if (attn_k4_applies(G, s) && T < (1LL << 30) &&
-      ((reinterpret_cast<uintptr_t>(kp) | reinterpret_cast<uintptr_t>(vp)) & 3u) == 0 &&
-      ((reinterpret_cast<uintptr_t>(kn) | reinterpret_cast<uintptr_t>(vn)) & 1u) == 0)
+  // matrix-core kernel; the payload quarters of k <= 4 are read as aligned
+  // dwords or 16-bit halves
+  if (use_k4(n_groups, G, T, s) && norms2 &&
+      (s.k > 4 || ((reinterpret_cast<uintptr_t>(kp) | reinterpret_cast<uintptr_t>(vp)) & 3u) == 0))
     return launch_attn_k4(q, q_dtype, kp, kn, vp, vn, n_groups, G, T, T_stride, s, R, C, scale,
                           out, ws, st);
+  if (attn_w4_applies(G, s) && T < (1LL << 30) && norms2)
+    return launch_attn_w4(q, q_dtype, kp, kn, vp, vn, n_groups, T, T_stride, R, C, scale, out, ws,
+                          st);
 #define FIBQ_ATTN_CASE(DD, KK)                                                                 \
   if (s.d == DD && s.k == KK)                                                               \
     return launch_attn_t<DD, KK>(q, q_dtype, kp, kn, vp, vn, n_groups, G, T, T_stride, s, R, C, \

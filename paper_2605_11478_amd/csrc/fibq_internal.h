@@ -73,10 +73,9 @@ int launch_encode_big(const void* x, int dtype, int64_t n_vec, int64_t stride, c
                       const float* R, const float* C, uint8_t* payload, uint16_t* norms,
                       void* stream, int n_cu);
 size_t attn_workspace_bytes(int64_t n_groups, int G, int64_t T, Shape s);
-bool attn_fast_applies(int G, const Shape& s);
-size_t attn_fast_workspace_bytes(int64_t n_groups, int64_t T);
 bool attn_w4_applies(int G, const Shape& s);
 bool attn_k4_applies(int G, const Shape& s);
+bool attn_k4_fits(int64_t n_groups, int64_t T);
 size_t attn_k4_workspace_bytes(int64_t n_groups, int64_t T, const Shape& s);
 size_t attn_w4_workspace_bytes(int64_t n_groups, int64_t T);
 // The library's static attention scratch on the current device (its address

@@ -625,6 +625,44 @@ def test_attention_k4_shapes(d, k, N, G, T, T_stride, fp16_cb, qmul, device):
     gh.check_attention(o, ref)
 
 
+@pytest.mark.parametrize("d,k,N,G,n_g,T,T_stride,fp16_cb", [
+    (64, 8, 64, 8, 2, 1024, 1024, True), (64, 8, 64, 8, 2, 1025, 1030, True),
+    (64, 8, 64, 3, 300, 65, 67, False), (64, 8, 16, 4, 1, 33, 33, True),
+    (64, 8, 256, 8, 5, 257, 257, True), (64, 8, 1024, 1, 2, 31, 40, False),
+    (64, 8, 4096, 5, 2, 1500, 1501, True), (64, 16, 256, 2, 3, 700, 703, True),
+    (64, 16, 2048, 8, 1, 129, 129, False), (64, 4, 1024, 7, 2, 1300, 1300, False),
+    (64, 4, 16, 4, 2, 96, 96, True), (128, 8, 256, 8, 2, 256, 256, True),
+    (128, 8, 4096, 1, 2, 289, 291, True), (128, 16, 512, 4, 2, 600, 600, False),
+    (64, 4, 256, 8, 700, 33, 33, True), (64, 4, 256, 2, 2100, 40, 41, True),
+    (128, 4, 256, 8, 300, 270, 271, True), (64, 2, 16, 1, 257, 255, 255, False)])
+def test_attention_row_codes(d, k, N, G, n_g, T, T_stride, fp16_cb, device):
+    """The matrix-core attention over 4-dim rows: index widths of 4 to 12 bits
+    read as unaligned payload quarters, every launch plan (one workgroup per
+    group up to its limits and one past them, split ranges with groups that
+    cross wavefronts and workgroups, separate query preparation), ragged ends.
+
+    Bound: q~ and the weights carry 22 bits, products and sums are float32; a
+    score's error is a few roundings relative to sum |q_i k_i| <= |q| |k|, and
+    a relative error of the weights passes to the output (the values' errors
+    are of the same size): 2^-20 |q| |k| scale log2(e) + 2^-18."""
+    R, C = oracle_rotation(d), quick_codebook(d, k, N)
+    if fp16_cb:
+        C = C.astype(np.float16).astype(np.float32)
+    Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
+    rng = np.random.default_rng(T + d + G + N)
+    q, kp, hk, vp, hv = _random_attention_inputs(rng, n_g, T_stride, d, k, N, G, kscale=2.0)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(device)
+    _say(f"[edge] attention rows d={d} k={k} N={N} G={G} n_g={n_g} T={T}")
+    o = fq.attn_decode(dev(q), dev(kp), dev(occ.fp16_bits(hk).view(np.int16)), dev(vp),
+                       dev(occ.fp16_bits(hv).view(np.int16)), T, k, N, Rd, Cd).cpu().numpy()
+    some = sorted({0, n_g // 2, n_g - 1, n_g // 3})
+    ref = gh.oracle_group_attention(q[some].astype(np.float64), kp[some], occ.fp16_bits(hk)[some],
+                                    vp[some], occ.fp16_bits(hv)[some], R, C, N, T)
+    rel = np.linalg.norm(o[some] - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    reach = np.linalg.norm(q[some], axis=-1).max() * hk.astype(np.float64).max() / np.sqrt(d)
+    assert rel.max() <= 2.0 ** -20 * reach * 1.4427 + 2.0 ** -18, rel.max()
+
+
 def test_attention_zero_query_is_mean_value(device):
     """q = 0: every score is 0, the output is the mean decoded value."""
     d, k, N, G, T = 128, 4, 4096, 4, 300
