@@ -295,9 +295,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_shells_kernel(
   encode_body<IN, D, K, CG, true>(x, n_vec, stride, R, C, N, W, P, payload, norms, L, &sm);
 }
 
-// Exhaustive encoder for codebooks read from global memory at d = 64 and
-// k >= 32 (one or two blocks per vector; at k = 8, 16 the general kernel's
-// scalar-load scan measured faster).  The general kernel's wavefronts each
+// Exhaustive encoder for codebooks read from global memory at k = d = 64.
+// The general kernel's wavefronts each
 // stream the whole codebook once per block through scalar loads; here a
 // workgroup stages the codebook in 32 KB chunks in LDS with coalesced loads
 // and its 256 vectors scan every chunk, each thread keeping the best two
@@ -787,6 +786,11 @@ static int num_cus() {
   return n;
 }
 
+// the exhaustive general encoder's block dimensions; k = 4, 8, 16 and 32 are
+// encode_gen.hip's (147456 rows of k = 8, N = 1024: 1124 us here, 91 there)
+template <int K>
+constexpr bool scans_all() { return K < 4 || K == 64; }
+
 template <typename IN, int D, int K, bool CG>
 static int launch_encode_cg(const void* x, int64_t n_vec, int64_t stride, const Shape& s,
                             const float* R, const float* C, uint8_t* payload, uint16_t* norms,
@@ -795,8 +799,9 @@ static int launch_encode_cg(const void* x, int64_t n_vec, int64_t stride, const 
   const size_t lds = sizeof(PT) * D * D + (sm ? 8 * kMaxShells : 0) +
                      sizeof(float) * (size_t)((CG ? 0 : s.N * K) + s.N + 4) +
                      (size_t)kEncThreads * s.P;
-  const void* kern = sm ? reinterpret_cast<const void*>(&encode_shells_kernel<IN, D, K, CG>)
-                        : reinterpret_cast<const void*>(&encode_kernel<IN, D, K, CG>);
+  const void* kern = reinterpret_cast<const void*>(&encode_shells_kernel<IN, D, K, CG>);
+  if constexpr (scans_all<K>())
+    if (!sm) kern = reinterpret_cast<const void*>(&encode_kernel<IN, D, K, CG>);
   hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return (int)e;
   const int64_t ntiles = (n_vec + kEncThreads - 1) / kEncThreads;
@@ -806,10 +811,11 @@ static int launch_encode_cg(const void* x, int64_t n_vec, int64_t stride, const 
     hipLaunchKernelGGL((encode_shells_kernel<IN, D, K, CG>), dim3(grid), dim3(kEncThreads), lds,
                        st, static_cast<const IN*>(x), n_vec, stride, R, C, s.N, s.w, s.P, payload,
                        norms, L, *sm);
-  else
-    hipLaunchKernelGGL((encode_kernel<IN, D, K, CG>), dim3(grid), dim3(kEncThreads), lds, st,
-                       static_cast<const IN*>(x), n_vec, stride, R, C, s.N, s.w, s.P, payload,
-                       norms);
+  if constexpr (scans_all<K>())
+    if (!sm)
+      hipLaunchKernelGGL((encode_kernel<IN, D, K, CG>), dim3(grid), dim3(kEncThreads), lds, st,
+                         static_cast<const IN*>(x), n_vec, stride, R, C, s.N, s.w, s.P, payload,
+                         norms);
   return (int)hipGetLastError();
 }
 
@@ -837,7 +843,7 @@ template <typename IN, int D, int K>
 static int launch_encode_t(const void* x, int64_t n_vec, int64_t stride, const Shape& s,
                            const float* R, const float* C, uint8_t* payload, uint16_t* norms,
                            int L, const ShellMids* sm, hipStream_t st) {
-  if constexpr (D == 64 && K >= 32) {  // large blocks and codebooks: chunked through LDS
+  if constexpr (D == 64 && K == 64) {  // the full-vector code, large codebooks: chunked through LDS
     if (!sm && s.N * K > kCbLds && s.N % (8192 / K) == 0 &&
         reinterpret_cast<uintptr_t>(C) % 16 == 0)
       return launch_encode_chunked<IN, D, K>(x, n_vec, stride, s, R, C, payload, norms, st);
@@ -883,8 +889,8 @@ int launch_encode(const void* x, int dtype, int64_t n_vec, int64_t stride, Shape
     return launch_encode_mfma(x, n_vec, stride, s, R, C, payload, norms, stream, num_cus());
   if (encode_mf4_applies(dtype, s, x, stride, R, payload, norms))
     return launch_encode_mf4(x, dtype, n_vec, stride, s, R, C, payload, norms, stream, num_cus());
-  if (encode_big_applies(dtype, s, x, stride, R, C, payload))
-    return launch_encode_big(x, dtype, n_vec, stride, s, R, C, payload, norms, stream, num_cus());
+  if (encode_gen_applies(s))
+    return launch_encode_gen(x, dtype, n_vec, stride, s, R, C, payload, norms, stream, num_cus());
   return dispatch_dtype(x, dtype, n_vec, stride, s, R, C, payload, norms, 1, nullptr, st);
 }
 

@@ -67,9 +67,8 @@ bool encode_mf4_applies(int dtype, const Shape& s, const void* x, int64_t stride
 int launch_encode_mf4(const void* x, int dtype, int64_t n_vec, int64_t stride, const Shape& s,
                       const float* R, const float* C, uint8_t* payload, uint16_t* norms,
                       void* stream, int n_cu);
-bool encode_big_applies(int dtype, const Shape& s, const void* x, int64_t stride,
-                        const float* R, const float* C, const uint8_t* payload);
-int launch_encode_big(const void* x, int dtype, int64_t n_vec, int64_t stride, const Shape& s,
+bool encode_gen_applies(const Shape& s);
+int launch_encode_gen(const void* x, int dtype, int64_t n_vec, int64_t stride, const Shape& s,
                       const float* R, const float* C, uint8_t* payload, uint16_t* norms,
                       void* stream, int n_cu);
 size_t attn_workspace_bytes(int64_t n_groups, int G, int64_t T, Shape s);

@@ -405,13 +405,12 @@ def test_encode_k2_n64_grid_edge_cases(dtype, device):
     (64, torch.float32, 1024, "fp16"), (64, torch.bfloat16, 4096, "wide"),
     (64, torch.bfloat16, 512, "plain")])
 def test_encode_large_codebook_path(d, dtype, N, variant, device):
-    """k = 4 with d = 128, N >= 1024 or d = 64, N in {256, 1024, 4096} (the
-    matrix-core screen with its float64 certificate and full float64
-    re-score; d = 64, N = 512 takes the general encoder): norms over several
-    decades, zero rows, strided rows, a ragged count, codebooks with and
-    without exact binary16 entries, duplicated codewords (exact ties: lowest
-    index), and a codebook outside the screen's range (|c| > 2: every block
-    re-scored)."""
+    """Larger codebooks at k = 4 (the matrix-core screen with its certificate
+    and full float64 re-score; 256 codewords of 16-bit rows at d = 64 have
+    their own encoder): norms over several decades, zero rows, strided rows, a
+    ragged count, codebooks with and without exact binary16 entries,
+    duplicated codewords (exact ties: lowest index), and a codeword longer
+    than any block."""
     k = 4
     R = oracle_rotation(d)
     C = quick_codebook(d, k, N).copy()
@@ -441,6 +440,55 @@ def test_encode_large_codebook_path(d, dtype, N, variant, device):
     assert not p.cpu().numpy()[3].any() and int(gh.bits_u16(nrm)[3]) == 0
     p2, n2 = fq.encode(xd.contiguous(), k, N, Rd, Cd)
     assert torch.equal(p, p2) and torch.equal(nrm, n2)
+
+
+@pytest.mark.parametrize("d,k,N,dtype,n,variant", [
+    (64, 8, 2, torch.float32, 1, "plain"), (64, 8, 16, torch.float16, 17, "dup"),
+    (64, 8, 32, torch.float32, 64, "fp16"), (64, 8, 64, torch.float16, 333, "strided"),
+    (64, 8, 512, torch.bfloat16, 1037, "dup"), (64, 8, 8192, torch.float16, 50, "plain"),
+    (64, 16, 128, torch.float32, 133, "strided"), (64, 16, 4096, torch.bfloat16, 65, "wide"),
+    (64, 32, 64, torch.float16, 47, "plain"), (64, 32, 2048, torch.float32, 129, "dup"),
+    (64, 4, 2, torch.bfloat16, 100, "fp16"), (64, 4, 128, torch.float32, 97, "strided"),
+    (64, 4, 512, torch.float16, 1037, "dup"), (128, 4, 64, torch.bfloat16, 31, "strided"),
+    (128, 4, 256, torch.float32, 205, "wide"), (128, 8, 256, torch.float16, 513, "dup"),
+    (128, 8, 8192, torch.bfloat16, 33, "fp16"), (128, 16, 32, torch.float32, 15, "plain"),
+    (128, 16, 1024, torch.float16, 49, "strided")])
+def test_encode_matrix_core_general(d, k, N, dtype, n, variant, device):
+    """The matrix-core encoder for any N at k = 4 to 32: one and two tiles of
+    codewords, codebooks that pass through LDS in chunks, ragged batches of 16
+    rows, rows at odd element offsets and strides, duplicated codewords (exact
+    ties: lowest index), codebooks with residuals and with |c| > 16 (every
+    block in float64), zero rows and rows with an infinity."""
+    R = oracle_rotation(d)
+    rng = np.random.default_rng(d + k + N)
+    C = rng.standard_normal((N, k)) * rng.uniform(0.4, 1.0, (N, 1)) * np.sqrt(1.0 / d)
+    C = C.astype(np.float16 if variant in ("fp16", "dup") else np.float32).astype(np.float32)
+    if variant == "dup":  # in two tiles (or twice in one), and next to each other
+        C[N - 2] = C[N // 3]
+        C[1] = C[0]
+    elif variant == "wide":
+        C[N // 2] *= 20.0 / np.linalg.norm(C[N // 2])
+    Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
+    g = torch.Generator().manual_seed(N + n)
+    pad = 3 if variant == "strided" else 0  # elements: no 4-byte alignment for 16-bit rows
+    x = torch.randn(n, d + pad, generator=g) * torch.exp(2 * torch.randn(n, 1, generator=g))
+    zero = n // 2
+    x[zero] = 0
+    x = x.to(dtype)
+    xd = x.to(device)[:, pad:]
+    _say(f"[edge] matrix-core encoder d={d} k={k} N={N} {dtype} n={n} {variant}")
+    p, nrm = fq.encode(xd, k, N, Rd, Cd)
+    torch.cuda.synchronize()
+    ne, nt, _, _ = gh.check_encode(gh.host_f64(x[:, pad:]), R, C, N, p, nrm)
+    _say(f"  {ne} exact indices, {nt} accepted near-ties")
+    assert not p[zero].any()
+    if n > 16:  # an infinite row stores an infinite header and indices 0; the others stay
+        y = xd.clone()
+        y[3, 5] = float("inf")
+        p2, n2 = fq.encode(y, k, N, Rd, Cd)
+        keep = torch.arange(n, device=device) != 3
+        assert torch.equal(p2[keep], p[keep]) and torch.equal(n2[keep], nrm[keep])
+        assert not p2[3].any() and int(gh.bits_u16(n2)[3]) == 0x7C00
 
 
 @pytest.mark.parametrize("k,N", [(8, 16), (4, 256)])
