@@ -128,13 +128,14 @@ static Plan make_plan(int64_t n_groups, int64_t T, int D, int max_wgs) {
   p.whole = n_groups <= max_wgs &&
             p.upg <= (D == 64 && n_groups <= kMaxWgs / 2 ? 2 * kWavesWhole : kWaves);
   if (p.whole) {
-    p.wgs = (int)n_groups;
+    p.wgs = n_groups > 0 ? (int)n_groups : 1;
     p.wpg = p.upg <= kWaves ? kWaves : whole_waves(D);
     p.slots = 1;
     p.pro = true;
   } else {
     const int64_t want = (units + kWaves - 1) / kWaves;
     p.wgs = (int)(want < max_wgs ? want : max_wgs);
+    if (p.wgs < 1) p.wgs = 1;  // (no groups)
     p.wpg = kWaves;
     const int64_t per = (units + p.wgs - 1) / p.wgs;  // units of a workgroup, at most
     p.slots = (int)(per <= 1 ? 1 : (per - 2) / p.upg + 2);

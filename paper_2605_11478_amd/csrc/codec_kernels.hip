@@ -786,8 +786,9 @@ static int num_cus() {
   return n;
 }
 
-// the exhaustive general encoder's block dimensions; k = 4, 8, 16 and 32 are
-// encode_gen.hip's (147456 rows of k = 8, N = 1024: 1124 us here, 91 there)
+// the exhaustive general encoder's block dimensions: k = d = 64, and k = 1, 2
+// for N > 2048; the others are encode_gen.hip's (147456 rows of k = 8,
+// N = 1024: 1124 us here, 91 there)
 template <int K>
 constexpr bool scans_all() { return K < 4 || K == 64; }
 
@@ -881,16 +882,37 @@ static int dispatch_dtype(const void* x, int dtype, int64_t n_vec, int64_t strid
   return (int)hipErrorInvalidValue;
 }
 
+// Up to so many rows (on 256 compute units) encode_gen.hip is faster than the
+// tile kernels of the specialised codes, which build their tables for
+// 12 wavefronts per compute unit first and cost the same from one row to a
+// tile per wavefront (98304 rows).  us, tile kernel / encode_gen, bf16 d = 64:
+//   (8, 64)  32 rows 48.6 /  7.1, 147456 105 / 51.5, 350000 117 / 117
+//   (8, 16)  4096 rows 11.4 / 7.5, 16384 11.6 / 9.8
+//   (4, 256) 32 rows 18.7 / 7.1, 4096 32.3 / 8.7, 49152 34.4 / 30.5, 65536 34.6 / 36.2
+//   (4, 64)  4096 rows 20.2 / 7.7, 16384 20.0 / 15.5, 65536 20.3 / 29.6
+//   (4, 16)  4096 rows 11.8 / 7.5, 16384 12.2 / 14.8
+//   (2, 256) 4096 rows 97.1 / 22.4, 65536 112 / 101
+//   (2, 64)  4096 rows 29.6 / 10.7, 32768 29.8 / 24.2, 65536 30.3 / 39.8
+//   (2, 16)  4096 rows 14.9 / 7.9, 16384 15.4 / 11.4
+static int64_t few_rows(const Shape& s) {
+  if (s.k == 8) return s.N == 64 ? 327680 : 16384;
+  if (s.k == 4) return s.N == 256 ? 57344 : s.N == 64 ? 28672 : 8192;
+  return s.N == 256 ? 65536 : s.N == 64 ? 40960 : 20480;
+}
+
 int launch_encode(const void* x, int dtype, int64_t n_vec, int64_t stride, Shape s,
                   const float* R, const float* C, uint8_t* payload, uint16_t* norms,
                   void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (encode_mfma_applies(dtype, s, x, stride, R, payload, norms))
-    return launch_encode_mfma(x, n_vec, stride, s, R, C, payload, norms, stream, num_cus());
-  if (encode_mf4_applies(dtype, s, x, stride, R, payload, norms))
-    return launch_encode_mf4(x, dtype, n_vec, stride, s, R, C, payload, norms, stream, num_cus());
+  const int n_cu = num_cus();
+  if (!encode_gen_applies(s) || n_vec > few_rows(s) * n_cu / 256) {
+    if (encode_mfma_applies(dtype, s, x, stride, R, payload, norms))
+      return launch_encode_mfma(x, n_vec, stride, s, R, C, payload, norms, stream, n_cu);
+    if (encode_mf4_applies(dtype, s, x, stride, R, payload, norms))
+      return launch_encode_mf4(x, dtype, n_vec, stride, s, R, C, payload, norms, stream, n_cu);
+  }
   if (encode_gen_applies(s))
-    return launch_encode_gen(x, dtype, n_vec, stride, s, R, C, payload, norms, stream, num_cus());
+    return launch_encode_gen(x, dtype, n_vec, stride, s, R, C, payload, norms, stream, n_cu);
   return dispatch_dtype(x, dtype, n_vec, stride, s, R, C, payload, norms, 1, nullptr, st);
 }
 

@@ -1,6 +1,7 @@
 // Encoder for block dimensions k = 4, 8, 16 and 32 (Eq. encode of Sec. 3.1)
 // with the nearest-codeword search as a dense contraction on the matrix cores:
-// every N, input type, row stride and alignment, d = 64 or 128 (k = 32: 64).
+// every N, input type, row stride and alignment, d = 64 or 128 (k = 32: 64);
+// and for k = 1 and 2 with a scan (scan_kernel below).
 //
 // A wavefront encodes 16 vectors per batch:
 //
@@ -149,11 +150,6 @@ __device__ __forceinline__ void split8(const float* y, uint32_t (&hi)[4], uint32
   }
 }
 
-struct Consts {      // of the codebook, for the bounds
-  float cn, c1, clo; // largest |c|_2, |c|_1, |c - fp16(c)|_2
-  uint32_t bad;      // an entry out of the scaled binary16 range
-};
-
 // Float64 nearest codeword of block m of one row, by the whole wavefront.
 template <typename IN, int D, int K>
 __device__ __noinline__ int scan64(const IN* __restrict__ row, const float* __restrict__ R,
@@ -190,16 +186,87 @@ __device__ __noinline__ int scan64(const IN* __restrict__ row, const float* __re
   return bj;
 }
 
-// NC: codewords in LDS at a time (N rounded up to 64, or a chunk of it when CH)
-template <typename IN, int D, int K, int WAVES, bool CH>
+// Norm and rotation of 16 vectors: lane group g reads quarter g of row
+// lane % 16 (xrow).  Returns nu, sets inv = 1 / nu (0 for a zero row) and
+// yf[4 rt + i] = scale times row 4 i + g of rotation tile rt, whose row p is
+// Pi's row prow(rt) in the lanes with lane % 16 = p (the float64 product leaves
+// output row 4 i + g of a tile in register i of lane group g).
+template <typename IN, int D, int NT, typename F>
+__device__ __forceinline__ double rotate(const IN* xrow, const float* __restrict__ R, float scale,
+                                         F prow, float (&yf)[4 * NT], double& inv) {
+  constexpr int NQ = D / 4;  // elements of a row per lane
+  const int g = (threadIdx.x & 63) >> 4;
+  float xf[NQ];
+  load_row<IN, NQ>(xrow + NQ * g, xf);
+  double ss = 0.0;
+#pragma unroll
+  for (int s = 0; s < NQ; ++s) ss = fma((double)xf[s], (double)xf[s], ss);
+  ss += xor64(ss, 16);
+  ss += xor64(ss, 32);
+  const double nu = sqrt(ss);
+  inv = nu > 0.0 ? 1.0 / nu : 0.0;
+  const double sc = inv * (double)scale;
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt) {
+    const float* pr = R + (size_t)prow(rt) * D + NQ * g;
+    d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < NQ; s += 4) {
+      f4 p;
+      __builtin_memcpy(&p, pr + s, 16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p[e], (double)xf[s + e], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      yf[4 * rt + i] = (float)(acc[i] * sc);
+      // (keeps the binary16 parts from being converted from float64, which
+      // is a software sequence)
+      asm("" : "+v"(yf[4 * rt + i]));
+    }
+  }
+  return nu;
+}
+
+// Lane v < 16 writes the bit stream of its vector from its indices.
+template <int NB>
+__device__ __forceinline__ void pack_row(const uint16_t* idx, bool zero, int W, uint8_t* dst) {
+  uint64_t bits = 0;
+  int nb = 0, at = 0;
+#pragma unroll 8
+  for (int m = 0; m < NB; ++m) {
+    bits |= (uint64_t)(zero ? 0u : (uint32_t)idx[m]) << nb;
+    nb += W;
+    if (nb >= 32) {
+      const uint32_t wv = (uint32_t)bits;
+      __builtin_memcpy(dst + at, &wv, 4);
+      at += 4;
+      bits >>= 32;
+      nb -= 32;
+    }
+  }
+  for (; nb > 0; nb -= 8, bits >>= 8) dst[at++] = (uint8_t)bits;
+}
+
+// lane groups' blocks: a wavefront's rotation leaves 4 blocks (64 columns, two
+// operands) for each of these
+constexpr int quads(int D, int K) { return K <= 16 ? D / (4 * K) : 1; }
+
+// NC: codewords in LDS at a time (N rounded up to 64, or a chunk of it when
+// CH).  SP: quads(D, K) wavefronts share a batch, one quad of blocks each (few
+// rows: more wavefronts, a shorter chain and less code for each).
+template <typename IN, int D, int K, int WAVES, bool CH, bool SP>
 __global__ __launch_bounds__(64 * WAVES) void encode_kernel(
     const IN* __restrict__ x, int64_t n_vec, int64_t stride, const float* __restrict__ R,
     const float* __restrict__ C, int N, int NC, int W, int P, uint32_t kmask_s,
     uint8_t* __restrict__ payload, uint16_t* __restrict__ norms) {
-  constexpr int NQ = D / 4;                     // elements of a row per lane
-  constexpr int NT = D / 16;                    // row tiles of the rotation
   constexpr int NB = D / K;                     // blocks per vector
-  constexpr int NOP = 16 * NB / 32;             // 32-block operands of a batch
+  constexpr int QN = SP ? quads(D, K) : 1;      // wavefronts of a batch
+  constexpr int QW = quads(D, K) / QN;          // quads of a wavefront
+  constexpr int NT = K <= 16 ? QW * (K / 4) : 4;  // its row tiles of the rotation
+  constexpr int NOP = K <= 16 ? 2 * QW : 1;     // its 32-block operands
+  static_assert(!(SP && CH), "");
   constexpr int OPS = NOP < kOps ? NOP : kOps;  // screened together
   constexpr int NM = K <= 8 ? 1 : K / 8;        // matrix products per score
   constexpr int NA = K == 32 ? 2 : 1;           // A operands of a tile
@@ -208,82 +275,68 @@ __global__ __launch_bounds__(64 * WAVES) void encode_kernel(
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* rows = smem;
   unsigned char* nrms = smem + rows_bytes<K>(NC);
-  __shared__ uint32_t cst[4];
-  __shared__ uint16_t stage[WAVES][kVec][NB];  // chosen indices of a batch
+  __shared__ __align__(16) float cst[WAVES][4];                   // each wavefront's constants of the codebook
+  __shared__ uint16_t stage[WAVES / QN][kVec][NB];  // chosen indices of a batch
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int q0 = wave % QN, wb = wave / QN;         // quad, batch of the workgroup
   const int h = lane >> 5, c32 = lane & 31, g = lane >> 4, v16 = lane & 15;
 
-  // codewords c0 .. c0 + NC - 1 as scaled binary16 rows and norms; rows past N
-  // score lowest (finite: a tile number in -inf's mantissa would be a NaN)
-  auto stage_rows = [&](int c0) {
-    for (int i = tid; i < NC * (K / E8); i += 64 * WAVES) {
-      const int j = i / (K / E8), p = i % (K / E8);
-      float cv[E8] = {};
-      if (c0 + j < N) __builtin_memcpy(cv, C + (size_t)(c0 + j) * K + E8 * p, 4 * E8);
-      _Float16 r[E8];
-#pragma unroll
-      for (int e = 0; e < E8; ++e) r[e] = (_Float16)(cv[e] * kC);
-      __builtin_memcpy(__builtin_assume_aligned(rows + row_at<K>(j) + 16 * p, 2 * E8), r, 2 * E8);
-    }
-    for (int j = tid; j < NC; j += 64 * WAVES) {
+  // codewords c0 .. c0 + NC - 1 as scaled binary16 rows and norms (rows past N
+  // score lowest; finite: a tile number in -inf's mantissa would be a NaN), and
+  // their constants for the bounds
+  float c2 = 0.0f, c1 = 0.0f, cl = 0.0f;
+  bool odd = false;  // a codeword out of range
+  auto stage_rows = [&](int c0, bool put) {
+    for (int j = tid; j < (put ? NC : N); j += 64 * WAVES) {
       float n = -3e38f;
-      if (c0 + j < N) {
-        double s = 0.0;
-#pragma unroll 8
-        for (int r = 0; r < K; ++r) {
-          const double v = (double)C[(size_t)(c0 + j) * K + r];
-          s = fma(v, v, s);
-        }
-        n = (float)(-0.5 * s * (double)kS);
-      }
-      *reinterpret_cast<float*>(nrms + nrm_at(j)) = n;
-    }
-  };
-
-  // ---- the codebook's constants
-  if (tid < 4) cst[tid] = 0u;
-  __syncthreads();
-  {
-    float c2 = 0.0f, c1 = 0.0f, cl = 0.0f;
-    uint32_t bad = 0u;
-    for (int j = tid; j < N; j += 64 * WAVES) {
-      float s2 = 0.0f, s1 = 0.0f, sl = 0.0f;
+      double s = 0.0;
+      float s1 = 0.0f, sl = 0.0f;
+      const bool in = c0 + j < N;
 #pragma unroll
-      for (int p = 0; p < K; p += 4) {
-        float cv[4];
-        __builtin_memcpy(cv, C + (size_t)j * K + p, 16);
+      for (int p = 0; p < K; p += E8) {
+        float cv[E8] = {};
+        if (in) __builtin_memcpy(cv, C + (size_t)(c0 + j) * K + p, 4 * E8);
+        _Float16 r[E8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float l = cv[e] - (float)(_Float16)(cv[e] * kC) * (1.0f / kC);
-          s2 = fmaf(cv[e], cv[e], s2);
+        for (int e = 0; e < E8; ++e) {
+          r[e] = (_Float16)(cv[e] * kC);
+          const float l = cv[e] - (float)r[e] * (1.0f / kC);
+          s = fma((double)cv[e], (double)cv[e], s);
           s1 += fabsf(cv[e]);
           sl = fmaf(l, l, sl);
         }
+        if (put)
+          __builtin_memcpy(__builtin_assume_aligned(rows + row_at<K>(j) + 2 * p, 2 * E8), r, 2 * E8);
       }
-      if (!(s2 <= 256.0f)) bad = 1u;  // |c| <= 16: operands in binary16 range
-      c2 = fmaxf(c2, s2);
+      if (in) n = (float)(-0.5 * s * (double)kS);
+      if (put) *reinterpret_cast<float*>(nrms + nrm_at(j)) = n;
+      odd |= !(s <= 256.0);  // |c| <= 16: operands in binary16 range
+      c2 = fmaxf(c2, (float)s);
       c1 = fmaxf(c1, s1);
       cl = fmaxf(cl, sl);
     }
-    c2 = wave_max(c2);
-    c1 = wave_max(c1);
-    cl = wave_max(cl);
-    bad = __any(bad) ? 1u : 0u;
-    if (lane == 0) {
-      atomicMax(&cst[0], __float_as_uint(c2));
-      atomicMax(&cst[1], __float_as_uint(c1));
-      atomicMax(&cst[2], __float_as_uint(cl));
-      atomicOr(&cst[3], bad);
-    }
-  }
-  if (!CH) stage_rows(0);
+  };
+  stage_rows(0, !CH);
+  c2 = wave_max(c2);
+  c1 = wave_max(c1);
+  cl = wave_max(cl);
+  odd = __any(odd);
+  if (lane == 0) *reinterpret_cast<f4*>(cst[wave]) = f4{c2, c1, cl, odd ? 1.0f : 0.0f};
   __syncthreads();
+#pragma unroll
+  for (int i = 0; i < WAVES; ++i) {
+    const f4 v = *reinterpret_cast<const f4*>(cst[i]);
+    c2 = fmaxf(c2, v[0]);
+    c1 = fmaxf(c1, v[1]);
+    cl = fmaxf(cl, v[2]);
+    odd |= v[3] != 0.0f;
+  }
   // (float32 sums of K terms: 2^-16 covers their rounding)
-  const float c2max = __uint_as_float(cst[0]) * (1.0f + 0x1p-16f);
+  const float c2max = c2 * (1.0f + 0x1p-16f);
   const float cn = sqrtf(c2max) * (1.0f + 0x1p-20f);
-  const float c1max = __uint_as_float(cst[1]) * (1.0f + 0x1p-16f);
-  const float clo = sqrtf(__uint_as_float(cst[2])) * (1.0f + 0x1p-16f);
-  const bool bad = cst[3] != 0u;
+  const float c1max = c1 * (1.0f + 0x1p-16f);
+  const float clo = sqrtf(cl) * (1.0f + 0x1p-16f);
+  const bool bad = odd;
   // bounds as (slope) |y_b| + (constant), scaled, with the 25 % margin
   const float a_s = 0x1p-18f * NM + 0x1p-21f, a_n = 0x1p-18f * NM + 0x1p-22f;
   const float a_r = (K + 4) * 0x1p-24f;
@@ -294,55 +347,26 @@ __global__ __launch_bounds__(64 * WAVES) void encode_kernel(
   const float epack = 1.25f * (float)(~kmask_s + 1u) * 0x1p-23f;
 
   const int64_t nbatch = (n_vec + kVec - 1) / kVec;
-  const int64_t nw = (int64_t)gridDim.x * WAVES;
-  for (int64_t b0 = (int64_t)blockIdx.x * WAVES; b0 < nbatch; b0 += nw) {
-    const int64_t bt = b0 + wave;
-    if (!CH && bt >= nbatch) break;   // (chunks: every wavefront reaches the barriers)
+  const int64_t nw = (int64_t)gridDim.x * (WAVES / QN);
+  for (int64_t b0 = (int64_t)blockIdx.x * (WAVES / QN); b0 < nbatch; b0 += nw) {
+    const int64_t bt = b0 + wb;
+    if (!CH && !SP && bt >= nbatch) break;  // (otherwise every wavefront reaches the barriers)
     const bool live = bt < nbatch;
     const int64_t v0 = (live ? bt : nbatch - 1) * kVec;
     const int64_t vl = v0 + v16 < n_vec ? v0 + v16 : n_vec - 1;  // clamped (ragged batch)
     const IN* xrow = x + vl * stride;
-    float xf[NQ];
-    load_row<IN, NQ>(xrow + NQ * g, xf);
-    double ss = 0.0;
-#pragma unroll
-    for (int s = 0; s < NQ; ++s) ss = fma((double)xf[s], (double)xf[s], ss);
-    ss += xor64(ss, 16);
-    ss += xor64(ss, 32);
-    const double nu = sqrt(ss);
-    const double inv = nu > 0.0 ? 1.0 / nu : 0.0;
-    if (g == 0 && live && v0 + v16 < n_vec)
-      norms[v0 + v16] = nu > 0.0 ? f64_to_f16_bits(nu) : (uint16_t)0;
-
-    // ---- y, scaled: yf[4 rt + i] is coordinate 4 (rt % (K/4)) + i of block
-    //      4 (rt / (K/4)) + g (k <= 16), or coordinate 16 (g / 2) + 4 rt + i of
-    //      block g % 2 (k = 32).  The float64 MFMA leaves output row 4 i + g of
-    //      a tile in register i of lane group g.
-    float yf[NQ];
+    // yf, scaled: yf[4 rt + i] is coordinate 4 (rt % (K/4)) + i of block
+    // 4 (q0 + rt / (K/4)) + g (k <= 16), or coordinate 16 (g / 2) + 4 rt + i of
+    // block g % 2 (k = 32)
+    float yf[4 * NT];
     const int pg = v16 & 3, pi = v16 >> 2;
-    const double sc = inv * (double)kY;
-#pragma unroll
-    for (int rt = 0; rt < NT; ++rt) {
-      const int prow = K <= 16 ? K * (4 * (rt / (K / 4)) + pg) + 4 * (rt % (K / 4)) + pi
-                               : 32 * (pg & 1) + 16 * (pg >> 1) + 4 * rt + pi;
-      const float* pr = R + (size_t)prow * D + NQ * g;
-      d4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int s = 0; s < NQ; s += 4) {
-        f4 p;
-        __builtin_memcpy(&p, pr + s, 16);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)p[e], (double)xf[s + e], acc, 0, 0, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        yf[4 * rt + i] = (float)(acc[i] * sc);
-        // (keeps the binary16 parts from being converted from float64, which
-        // is a software sequence)
-        asm("" : "+v"(yf[4 * rt + i]));
-      }
-    }
+    double inv;
+    const double nu = rotate<IN, D, NT>(xrow, R, kY, [&](int rt) {
+      return K <= 16 ? K * (4 * (q0 + rt / (K / 4)) + pg) + 4 * (rt % (K / 4)) + pi
+                     : 32 * (pg & 1) + 16 * (pg >> 1) + 4 * rt + pi;
+    }, yf, inv);
+    if (g == 0 && q0 == 0 && live && v0 + v16 < n_vec)
+      norms[v0 + v16] = nu > 0.0 ? f64_to_f16_bits(nu) : (uint16_t)0;
 
 #pragma unroll
     for (int o0 = 0; o0 < NOP; o0 += OPS) {
@@ -400,7 +424,7 @@ __global__ __launch_bounds__(64 * WAVES) void encode_kernel(
       for (int c0 = 0; c0 < N; c0 += NC) {
         if (CH) {
           __syncthreads();
-          stage_rows(c0);
+          stage_rows(c0, true);
           __syncthreads();
         }
         // Two tiles a round; the maxima of one operand's scores are taken
@@ -452,7 +476,7 @@ __global__ __launch_bounds__(64 * WAVES) void encode_kernel(
             fold(sp, tn + (i - 1) / OPS, b1[(i - 1) % OPS], b2[(i - 1) % OPS]);
             sp = sn;
           }
-          if constexpr (D == 64 && NM == 1) {  // (elsewhere the compiler's own order is as good)
+          if constexpr (D == 64 && NM == 1 && !SP) {  // (elsewhere the compiler's own order is as good)
             __builtin_amdgcn_sched_group_barrier(0x100, 2 * (NA + 4), 0);  // LDS reads
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);             // products
 #pragma unroll
@@ -545,7 +569,7 @@ __global__ __launch_bounds__(64 * WAVES) void encode_kernel(
         const float er = fmaf(er1, yn, er0), es = fmaf(es1, yn, es0);
         const bool cert = !bad && s1 - s2 > 2.0f * er &&
                           s1 - b2[o] > er + es + epack * fabsf(b2[o]);
-        const int m = K <= 16 ? 4 * ((o0 + o) / 2) + 2 * (o & 1) + (c32 >> 4) : (c32 >> 4);
+        const int m = K <= 16 ? 4 * (q0 + (o0 + o) / 2) + 2 * (o & 1) + (c32 >> 4) : (c32 >> 4);
         uint64_t pend = __ballot(!cert && h == 0 && live && nu > 0.0 && v0 + v16 < n_vec);
         while (pend) {
           const int cl = __builtin_ctzll(pend);
@@ -555,49 +579,131 @@ __global__ __launch_bounds__(64 * WAVES) void encode_kernel(
           const int fj = scan64<IN, D, K>(x + vv * stride, R, C, N, mm, shfl64(inv, cl & 15));
           if (c32 == cl) jj = fj;
         }
-        if (h == 0) stage[wave][v16][m] = (uint16_t)jj;
+        if (h == 0) stage[wb][v16][m] = (uint16_t)jj;
       }
     }
 
-    // ---- pack: lane v < 16 writes the bit stream of vector v (this wavefront's
-    //      own LDS writes precede its reads)
-    if (lane < 16 && live && v0 + lane < n_vec) {
-      uint8_t* dst = payload + (v0 + lane) * (int64_t)P;
-      const bool zero = !(nu > 0.0);
-      uint64_t bits = 0;
-      int nb = 0, at = 0;
+    // ---- pack: lane v < 16 writes the bit stream of vector v (without SP this
+    //      wavefront's own LDS writes precede its reads)
+    if (SP) __syncthreads();
+    if (lane < 16 && q0 == 0 && live && v0 + lane < n_vec)
+      pack_row<NB>(stage[wb][lane], !(nu > 0.0), W, payload + (v0 + lane) * (int64_t)P);
+    if (SP) __syncthreads();
+  }
+}
+
+// k = 1 and 2: the same norm and rotation, then each lane scans all N codewords
+// (float32, broadcast from LDS as (c_0, c_1, -|c|^2 / 2)) for its own blocks;
+// near ties as above.  One thread per vector with a float64 rotation on the
+// vector units took 55 us for 4095 fp32 rows of k = 2, N = 16 (16 workgroups;
+// here 7.5), 147 us for 147456 rows of k = 1, N = 16 (79) and 867 us for
+// 147456 fp32 rows of k = 2, N = 256 (212).  Bound by the scan's k + 4 vector
+// instructions per codeword and block, at small N by the rotation.
+template <typename IN, int D, int K, bool SP>
+__global__ __launch_bounds__(64 * (SP ? D / 16 : 4)) void scan_kernel(
+    const IN* __restrict__ x, int64_t n_vec, int64_t stride, const float* __restrict__ R,
+    const float* __restrict__ C, int N, int W, int P, uint8_t* __restrict__ payload,
+    uint16_t* __restrict__ norms) {
+  constexpr int WAVES = SP ? D / 16 : 4;
+  constexpr int QN = SP ? WAVES : 1;      // wavefronts of a batch
+  constexpr int NT = D / 16 / QN;         // row tiles of a wavefront
+  constexpr int NB = D / K, BT = 4 / K;   // blocks of a vector, of a lane and tile
+  extern __shared__ __align__(16) unsigned char smem[];
+  f4* cw = reinterpret_cast<f4*>(smem);   // N codewords
+  __shared__ float cmax[WAVES];
+  __shared__ uint16_t stage[WAVES / QN][kVec][NB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int q0 = wave % QN, wb = wave / QN, g = lane >> 4, v16 = lane & 15;
+  float c2 = 0.0f;
+  for (int j = tid; j < N; j += 64 * WAVES) {
+    const float a = C[j * K], b = K == 2 ? C[j * K + K - 1] : 0.0f;
+    const double n = (double)a * a + (double)b * b;
+    cw[j] = f4{a, b, (float)(-0.5 * n), 0.0f};
+    c2 = fmaxf(c2, n <= 3e38 ? (float)n : INFINITY);
+  }
+  c2 = wave_max(c2);
+  if (lane == 0) cmax[wave] = c2;
+  __syncthreads();
 #pragma unroll
-      for (int m = 0; m < NB; ++m) {
-        bits |= (uint64_t)(zero ? 0u : (uint32_t)stage[wave][lane][m]) << nb;
-        nb += W;
-        if (nb >= 32) {
-          const uint32_t wv = (uint32_t)bits;
-          __builtin_memcpy(dst + at, &wv, 4);
-          at += 4;
-          bits >>= 32;
-          nb -= 32;
-        }
+  for (int i = 0; i < WAVES; ++i) c2 = fmaxf(c2, cmax[i]);
+  // float32 scores of float32 y: (k + 4) roundings of |c| |y| + |c|^2 / 2, twice
+  const float er = 2.0f * 1.25f * (K + 4) * 0x1p-24f;
+  const float er1 = er * sqrtf(c2) * (1.0f + 0x1p-16f), er0 = er * 0.5f * c2;
+
+  const int64_t nbatch = (n_vec + kVec - 1) / kVec;
+  for (int64_t b0 = (int64_t)blockIdx.x * (WAVES / QN); b0 < nbatch;
+       b0 += (int64_t)gridDim.x * (WAVES / QN)) {
+    const int64_t bt = b0 + wb;
+    if (!SP && bt >= nbatch) break;
+    const int64_t v0 = bt * kVec;
+    const int64_t vl = v0 + v16 < n_vec ? v0 + v16 : n_vec - 1;  // clamped (ragged batch)
+    float yf[4 * NT];
+    double inv;
+    const double nu = rotate<IN, D, NT>(x + vl * stride, R, 1.0f, [&](int rt) {
+      return 16 * (q0 + rt) + 4 * (v16 & 3) + (v16 >> 2);
+    }, yf, inv);
+    if (g == 0 && q0 == 0 && v0 + v16 < n_vec)
+      norms[v0 + v16] = nu > 0.0 ? f64_to_f16_bits(nu) : (uint16_t)0;
+    float s1[NT * BT], s2[NT * BT];
+    int j1[NT * BT];
+#pragma unroll
+    for (int b = 0; b < NT * BT; ++b) { s1[b] = -INFINITY; s2[b] = -INFINITY; j1[b] = 0; }
+#pragma unroll 2
+    for (int j = 0; j < N; ++j) {
+      const f4 c = cw[j];
+#pragma unroll
+      for (int b = 0; b < NT * BT; ++b) {
+        float s = fmaf(c[0], yf[b * K], c[2]);
+        if (K == 2) s = fmaf(c[1], yf[b * K + K - 1], s);
+        j1[b] = s > s1[b] ? j : j1[b];
+        s2[b] = __builtin_amdgcn_fmed3f(s1[b], s2[b], s);
+        s1[b] = fmaxf(s1[b], s);
       }
-      for (; nb > 0; nb -= 8, bits >>= 8) dst[at++] = (uint8_t)bits;
     }
+#pragma unroll
+    for (int b = 0; b < NT * BT; ++b) {
+      const float y0 = yf[b * K], y1 = K == 2 ? yf[b * K + K - 1] : 0.0f;
+      const float yn = sqrtf(fmaf(y0, y0, y1 * y1)) * (1.0f + 0x1p-16f);
+      const bool cert = s1[b] - s2[b] > fmaf(er1, yn, er0);
+      const int m = (16 * (q0 + b / BT) + 4 * g) / K + b % BT;
+      uint64_t pend = __ballot(!cert && nu > 0.0 && v0 + v16 < n_vec);
+      while (pend) {
+        const int cl = __builtin_ctzll(pend);
+        pend &= pend - 1;
+        const int fj = scan64<IN, D, K>(x + (v0 + (cl & 15)) * stride, R, C, N,
+                                        __builtin_amdgcn_readlane(m, cl), shfl64(inv, cl));
+        if (lane == cl) j1[b] = fj;
+      }
+      stage[wb][v16][m] = (uint16_t)j1[b];
+    }
+    if (SP) __syncthreads();
+    if (lane < 16 && q0 == 0 && v0 + lane < n_vec)
+      pack_row<NB>(stage[wb][lane], !(nu > 0.0), W, payload + (v0 + lane) * (int64_t)P);
+    if (SP) __syncthreads();
   }
 }
 
 constexpr size_t kLds = 160 * 1024 - 8192;  // dynamic, beside the static arrays
+// Rows that leave at most this many wavefronts per SIMD when a batch is shared:
+// (d, k, N) = (64, 4, 256), 16384 rows 18.4 us shared, 19.5 not, 32768 rows
+// 27.3 / 24.4; (128, 4, 4096) 8192 rows 106 / 214, 32768 rows 330 / 228.
+constexpr int kSplitWaves = 4;
+constexpr int kScanN = 2048;  // k <= 2: codewords of 16 bytes in 32 KB of LDS
 
-template <typename IN, int D, int K, int WAVES, bool CH>
+template <typename IN, int D, int K, int WAVES, bool CH, bool SP>
 static int launch_w(const void* x, int64_t n_vec, int64_t stride, const Shape& s, const float* R,
                     const float* C, uint8_t* payload, uint16_t* norms, int nc, int wgs,
                     hipStream_t st) {
   const size_t lds = rows_bytes<K>(nc) + nrms_bytes(nc);
-  auto kern = encode_kernel<IN, D, K, WAVES, CH>;
+  auto kern = encode_kernel<IN, D, K, WAVES, CH, SP>;
   if (lds > 65536) {  // above the default dynamic LDS limit
     const hipError_t e = hipFuncSetAttribute((const void*)kern,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return (int)e;
   }
+  constexpr int PER = WAVES / (SP ? quads(D, K) : 1);  // batches of a workgroup
   const int64_t nbatch = (n_vec + kVec - 1) / kVec;
-  const int64_t want = (nbatch + WAVES - 1) / WAVES;
+  const int64_t want = (nbatch + PER - 1) / PER;
   const int grid = (int)(want < wgs ? want : wgs);
   const uint32_t kmask = s.N <= 4096 ? ~127u : ~511u;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * WAVES), lds, st, static_cast<const IN*>(x), n_vec,
@@ -610,12 +716,39 @@ static int launch_k(const void* x, int64_t n_vec, int64_t stride, const Shape& s
                     const float* C, uint8_t* payload, uint16_t* norms, int n_cu, hipStream_t st) {
   const int nc = (s.N + 63) & ~63;  // whole pairs of tiles
   const size_t lds = rows_bytes<K>(nc) + nrms_bytes(nc);
+  constexpr int Q = quads(D, K);
+  if constexpr (Q > 1) {
+    if (lds <= kLds && n_vec * Q <= (int64_t)kSplitWaves * kVec * 4 * n_cu)
+      return launch_w<IN, D, K, (Q < 4 ? 4 : Q), false, true>(x, n_vec, stride, s, R, C, payload, norms,
+                                                             nc, 1 << 30, st);
+  }
   if (lds <= 40 * 1024)  // small codebooks: 4-wavefront workgroups, several per compute unit
-    return launch_w<IN, D, K, 4, false>(x, n_vec, stride, s, R, C, payload, norms, nc, 3 * n_cu, st);
+    return launch_w<IN, D, K, 4, false, false>(x, n_vec, stride, s, R, C, payload, norms, nc,
+                                               3 * n_cu, st);
   if (lds <= kLds)
-    return launch_w<IN, D, K, 8, false>(x, n_vec, stride, s, R, C, payload, norms, nc, n_cu, st);
-  return launch_w<IN, D, K, 8, true>(x, n_vec, stride, s, R, C, payload, norms, 65536 / (2 * K), n_cu,
-                                     st);
+    return launch_w<IN, D, K, 8, false, false>(x, n_vec, stride, s, R, C, payload, norms, nc, n_cu, st);
+  return launch_w<IN, D, K, 8, true, false>(x, n_vec, stride, s, R, C, payload, norms, 65536 / (2 * K),
+                                            n_cu, st);
+}
+
+template <typename IN, int D, int K, bool SP>
+static int launch_scan(const void* x, int64_t n_vec, int64_t stride, const Shape& s, const float* R,
+                       const float* C, uint8_t* payload, uint16_t* norms, int n_cu,
+                       hipStream_t st) {
+  const int64_t nbatch = (n_vec + kVec - 1) / kVec, want = SP ? nbatch : (nbatch + 3) / 4;
+  const int grid = (int)(SP || want < 4 * n_cu ? want : 4 * n_cu);
+  hipLaunchKernelGGL((scan_kernel<IN, D, K, SP>), dim3(grid), dim3(64 * (SP ? D / 16 : 4)),
+                     (size_t)s.N * 16, st, static_cast<const IN*>(x), n_vec, stride, R, C, s.N, s.w,
+                     s.P, payload, norms);
+  return (int)hipGetLastError();
+}
+
+template <typename IN, int D, int K>
+static int launch_s(const void* x, int64_t n_vec, int64_t stride, const Shape& s, const float* R,
+                    const float* C, uint8_t* payload, uint16_t* norms, int n_cu, hipStream_t st) {
+  if (n_vec * (D / 16) <= (int64_t)kSplitWaves * kVec * 4 * n_cu)
+    return launch_scan<IN, D, K, true>(x, n_vec, stride, s, R, C, payload, norms, n_cu, st);
+  return launch_scan<IN, D, K, false>(x, n_vec, stride, s, R, C, payload, norms, n_cu, st);
 }
 
 template <typename IN>
@@ -627,12 +760,18 @@ static int launch_t(const void* x, int64_t n_vec, int64_t stride, const Shape& s
   FIBQ_GEN_CASE(64, 4) FIBQ_GEN_CASE(64, 8) FIBQ_GEN_CASE(64, 16) FIBQ_GEN_CASE(64, 32)
   FIBQ_GEN_CASE(128, 4) FIBQ_GEN_CASE(128, 8) FIBQ_GEN_CASE(128, 16)
 #undef FIBQ_GEN_CASE
+#define FIBQ_SCAN_CASE(DD, KK)  \
+  if (s.d == DD && s.k == KK) \
+    return launch_s<IN, DD, KK>(x, n_vec, stride, s, R, C, payload, norms, n_cu, st);
+  FIBQ_SCAN_CASE(64, 1) FIBQ_SCAN_CASE(64, 2) FIBQ_SCAN_CASE(128, 1) FIBQ_SCAN_CASE(128, 2)
+#undef FIBQ_SCAN_CASE
   return (int)hipErrorInvalidValue;
 }
 
 }  // namespace gen
 
 bool encode_gen_applies(const Shape& s) {
+  if (s.k <= 2) return (s.d == 64 || s.d == 128) && s.N <= gen::kScanN;
   return ((s.d == 64 || s.d == 128) && (s.k == 4 || s.k == 8 || s.k == 16)) ||
          (s.d == 64 && s.k == 32);
 }

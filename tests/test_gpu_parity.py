@@ -452,7 +452,13 @@ def test_encode_large_codebook_path(d, dtype, N, variant, device):
     (64, 4, 512, torch.float16, 1037, "dup"), (128, 4, 64, torch.bfloat16, 31, "strided"),
     (128, 4, 256, torch.float32, 205, "wide"), (128, 8, 256, torch.float16, 513, "dup"),
     (128, 8, 8192, torch.bfloat16, 33, "fp16"), (128, 16, 32, torch.float32, 15, "plain"),
-    (128, 16, 1024, torch.float16, 49, "strided")])
+    (128, 16, 1024, torch.float16, 49, "strided"),
+    # the scan of k = 1 and 2, and each form on both sides of its row limits
+    (64, 1, 2, torch.float32, 33, "plain"), (64, 1, 16, torch.float16, 16400, "strided"),
+    (64, 2, 16, torch.float32, 4095, "dup"), (64, 2, 2048, torch.bfloat16, 47, "wide"),
+    (128, 1, 8, torch.bfloat16, 8193, "plain"), (128, 2, 64, torch.float16, 8200, "strided"),
+    (64, 4, 256, torch.bfloat16, 16385, "plain"), (64, 8, 64, torch.bfloat16, 40000, "dup"),
+    (128, 8, 64, torch.float32, 16400, "plain"), (64, 2, 64, torch.bfloat16, 32, "dup")])
 def test_encode_matrix_core_general(d, k, N, dtype, n, variant, device):
     """The matrix-core encoder for any N at k = 4 to 32: one and two tiles of
     codewords, codebooks that pass through LDS in chunks, ragged batches of 16
@@ -489,6 +495,46 @@ def test_encode_matrix_core_general(d, k, N, dtype, n, variant, device):
         keep = torch.arange(n, device=device) != 3
         assert torch.equal(p2[keep], p[keep]) and torch.equal(n2[keep], nrm[keep])
         assert not p2[3].any() and int(gh.bits_u16(n2)[3]) == 0x7C00
+
+
+@pytest.mark.parametrize("k,N,dtype,n", [
+    (8, 16, torch.bfloat16, 20001), (8, 64, torch.bfloat16, 330007),
+    (4, 256, torch.bfloat16, 60011), (4, 256, torch.float16, 60011),
+    (4, 64, torch.float16, 30011), (4, 16, torch.bfloat16, 10013),
+    (2, 256, torch.bfloat16, 70001), (2, 64, torch.float16, 50021), (2, 16, torch.bfloat16, 30011)])
+def test_encode_tile_kernels_match_few_rows(k, N, dtype, n, device):
+    """The specialised codes' tile kernels take over from the general
+    matrix-core encoder above a number of rows: one call over many rows gives
+    the bytes of calls over few, for rows that fill and overflow the tile
+    kernels' near-tie queues (blocks at the midpoints of two codewords, rows
+    whose float32 sum of squares leaves its range), zero rows and ordinary
+    ones, and a sample of them is the oracle's."""
+    d = 64
+    R = oracle_rotation(d)
+    C = quick_codebook(d, k, N).astype(np.float16).astype(np.float32)
+    Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
+    g = torch.Generator().manual_seed(n)
+    x = torch.randn(n, d, generator=g) * torch.exp(torch.randn(n, 1, generator=g))
+    rng = np.random.default_rng(n)
+    mid = 0.5 * (C[rng.integers(0, N, (512, d // k))] + C[rng.integers(0, N, (512, d // k))])
+    x[1000:1512] = torch.from_numpy(mid.reshape(512, d).astype(np.float32) @ R * 3.0)
+    big = 2e38 if dtype == torch.bfloat16 else 6e4
+    x[64:80] *= big / x[64:80].abs().max()            # 16 rows of one tile out of range
+    x[4000:9000:129] *= 2.0 ** -60 if dtype == torch.bfloat16 else 2.0 ** -14
+    x[96:128] = 0
+    x[5000] = 0
+    x = x.to(dtype)
+    xd = x.to(device)
+    _say(f"[edge] tile kernels against few rows k={k} N={N} {dtype} n={n}")
+    p, nrm = fq.encode(xd, k, N, Rd, Cd)
+    few = [fq.encode(c, k, N, Rd, Cd) for c in xd.split(4096)]
+    torch.cuda.synchronize()
+    assert torch.equal(nrm, torch.cat([f[1] for f in few]))
+    pf = torch.cat([f[0] for f in few])
+    assert torch.equal(p, pf), f"{int((p != pf).any(1).sum())} rows differ"
+    some = torch.cat([torch.arange(60, 132), torch.arange(1000, 1100), torch.arange(4000, 9000, 129),
+                      torch.arange(n - 40, n)])
+    gh.check_encode(gh.host_f64(x[some]), R, C, N, p[some.to(device)], nrm[some.to(device)])
 
 
 @pytest.mark.parametrize("k,N", [(8, 16), (4, 256)])
