@@ -1,7 +1,7 @@
 """FibQuant random-access KV-cache codec on MI355X (gfx950).
 
-Thin ctypes binding over ``libfibq.so`` (declared in ``include/fibq.h``):
-argument marshalling only.  Every step of the codec runs in the library's HIP
+Thin binding over ``libfibq.so`` (declared in ``include/fibq.h``; ctypes, and a
+compiled module for the calls on the decode path): argument marshalling only.  Every step of the codec runs in the library's HIP
 kernels; there is no CPU fallback, and a missing library raises.
 
 Tensors passed to device functions must be CUDA (HIP) tensors, contiguous,
@@ -24,7 +24,10 @@ FIBQ_EIO = -4
 FIBQ_EWORKSPACE = -5
 F32, F16, BF16 = 0, 1, 2
 
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
+
 _lib = None
+_fast = None  # the compiled binding, bound to the loaded library (see lib)
 
 
 class FibqError(RuntimeError):
@@ -77,7 +80,31 @@ def lib():
             fn.restype = res
             fn.argtypes = args
         _lib = L
+        _bind(L)
     return _lib
+
+
+def _bind(L):
+    """Give the compiled per-call path (csrc/binding.cpp) the library's entry
+    points.  It takes calls on device tensors that pass all checks and returns
+    None for any other, which the Python code below then checks and reports."""
+    global _fast
+    if not os.path.exists(BINDING_PATH):
+        raise ImportError(
+            f"{BINDING_PATH} is missing: build it with `python -m paper_2605_11478_amd.build`")
+    _torch()  # the module links against torch's libraries
+    from . import _binding
+    _binding.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in
+                    ("fibq_encode", "fibq_decode", "fibq_attn_decode",
+                     "fibq_attn_workspace_bytes", "fibq_payload_bytes")))
+    _fast = _binding
+
+
+def _raw_stream():
+    """The current device's current stream, as torch.cuda.current_stream()
+    gives it, without building a Stream object (2.7 us)."""
+    C = _torch()._C
+    return C._cuda_getCurrentRawStream(C._cuda_getDevice())
 
 
 def strerror(status):
@@ -248,6 +275,10 @@ def _check_x(x):
 
 def encode(x, k, N, R, C, payload=None, norms=None):
     """x [n, d] (rows may be strided) -> (payload uint8 [n, P], norm bits int16 [n])."""
+    if _fast is not None and getattr(x, "is_cuda", False):
+        done = _fast.encode(x, k, N, R, C, payload, norms, _raw_stream())
+        if done is not None:
+            return done
     _check_x(x)
     n, d = x.shape
     _check_rc(R, C, d, k, N)
@@ -314,6 +345,10 @@ def encode_list(x, k, N, L, K, T, mu, offsets, members, R, C, payload=None, norm
 
 def decode(payload, norms, d, k, N, R, C, token_ids=None, out=None):
     """-> x_hat float32 [n, d]; rows token_ids (int64, device) or all rows."""
+    if _fast is not None and getattr(payload, "is_cuda", False):
+        done = _fast.decode(payload, norms, d, k, N, R, C, token_ids, out, _raw_stream())
+        if done is not None:
+            return done
     torch = _torch()
     P = payload_bytes(d, k, N)
     _want(payload, "payload", (torch.uint8,), (None, P))
@@ -365,14 +400,19 @@ def attn_decode(q, k_payload, k_norms, v_payload, v_norms, T, k, N, R, C, scale=
 
     -> out float32 [n_groups, G, d].  ``workspace`` (uint8, at least
     ``attn_workspace_bytes`` bytes) may be reused across calls that do not
-    overlap in time; a fresh one is allocated (zero-filled) when omitted.
+    overlap in time; a fresh one is allocated when omitted.
     """
+    if _fast is not None and getattr(q, "is_cuda", False):
+        done = _fast.attn(q, k_payload, k_norms, v_payload, v_norms, T, k, N, R, C, scale,
+                          workspace, out, _raw_stream())
+        if done is not None:
+            return done
     torch = _torch()
     n_groups, G, d, T_stride, P, out = _check_attn(q, k_payload, k_norms, v_payload, v_norms,
                                                    T, k, N, R, C, out)
     need = attn_workspace_bytes(n_groups, G, T, d, k, N)
     if workspace is None:
-        workspace = torch.zeros((max(need, 1),), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty((max(need, 1),), dtype=torch.uint8, device=q.device)
     _want(workspace, "workspace", (torch.uint8,), (None,))
     if workspace.numel() < need:
         raise ValueError(f"workspace holds {workspace.numel()} bytes, {need} needed")

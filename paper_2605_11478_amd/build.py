@@ -1,4 +1,5 @@
-"""Build libfibq.so in-tree: host C++ with g++, HIP kernels with hipcc for gfx950.
+"""Build libfibq.so (host C++ with g++, HIP kernels with hipcc for gfx950) and the
+compiled binding _binding.so (g++ against torch's headers) in-tree.
 
 Usage: ``python -m paper_2605_11478_amd.build`` (or ``build()`` from Python).
 Always recompiles; objects go to ``paper_2605_11478_amd/_build/``.
@@ -14,6 +15,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(PKG, "libfibq.so")
+BINDING = os.path.join(PKG, "_binding.so")
 BUILD = os.path.join(PKG, "_build")
 
 HOST_SRC = ["api.cpp", "host_builder.cpp"]
@@ -46,6 +48,20 @@ def _run(cmd):
     return r.stdout
 
 
+def _binding_cmd():
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    inc = [a for p in cpp_extension.include_paths() for a in ("-isystem", p)]
+    lib = cpp_extension.library_paths()[0]
+    abi = f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", abi,
+            "-I", INCLUDE, "-I", sysconfig.get_paths()["include"], *inc,
+            os.path.join(CSRC, "binding.cpp"), "-o", BINDING + ".tmp", "-L", lib,
+            "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose=False):
     os.makedirs(BUILD, exist_ok=True)
     hipcc = _hipcc()
@@ -60,6 +76,7 @@ def build(verbose=False):
         o = os.path.join(BUILD, s + ".o")
         jobs.append([hipcc, *HIP_FLAGS, *inc, "-c", os.path.join(CSRC, s), "-o", o])
         objs.append(o)
+    jobs.append(_binding_cmd())
     with ThreadPoolExecutor(max_workers=4) as ex:
         outs = list(ex.map(_run, jobs))
     if verbose:
@@ -69,6 +86,7 @@ def build(verbose=False):
     tmp = OUT + ".tmp"
     _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", tmp, "-lpthread"])
     os.replace(tmp, OUT)
+    os.replace(BINDING + ".tmp", BINDING)
     return OUT
 
 

@@ -998,3 +998,64 @@ def test_encode_chunked_large_blocks_edge_cases(k, N, dtype, device):
     ne, nt, _, _ = gh.check_encode(gh.host_f64(x[:, :d]), R, C, N, p, nrm)
     _say(f"  {ne} exact indices, {nt} accepted near-ties")
     assert not p.cpu().numpy()[7].any() and int(gh.bits_u16(nrm)[7]) == 0
+
+
+def test_compiled_binding_agrees_with_python_checks(device, monkeypatch):
+    """The compiled per-call path accepts what the Python checks accept and
+    gives the same results, for strided rows, passed outputs (either 16-bit
+    norm type), token ids and a kept workspace; what they refuse on device
+    tensors still raises their error."""
+    d, k, N, G, T = 64, 4, 256, 4, 75
+    R, C = oracle_rotation(d), quick_codebook(d, k, N)
+    Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
+    g = torch.Generator().manual_seed(9)
+    x = torch.randn(2 * T, 2 * d, generator=g).to(torch.bfloat16).to(device)[:, :d]
+    q = torch.randn(2, G, d, generator=g).to(device)
+    P = fq.payload_bytes(d, k, N)
+    ids = torch.tensor([3, 0, 149, 77], device=device)
+
+    def calls():
+        p, n = fq.encode(x, k, N, Rd, Cd)
+        po = torch.empty(2 * T, P, dtype=torch.uint8, device=device)
+        no = torch.empty(2 * T, dtype=torch.uint16, device=device)
+        given = fq.encode(x, k, N, Rd, Cd, payload=po, norms=no)
+        assert given[0] is po and given[1] is no
+        kv = (p.view(2, T, P), n.view(2, T), p.view(2, T, P), n.view(2, T))
+        ws = torch.full((fq.attn_workspace_bytes(2, G, T, d, k, N) + 5,), 0xA5, dtype=torch.uint8,
+                        device=device)
+        out = torch.empty(2, G, d, device=device)
+        assert fq.attn_decode(q, *kv, T, k, N, Rd, Cd, workspace=ws, out=out) is out
+        return [p, n, po, no, out, fq.attn_decode(q, *kv, 50, k, N, Rd, Cd, scale=0.2),
+                fq.decode(p, n, d, k, N, Rd, Cd), fq.decode(p, n, d, k, N, Rd, Cd, token_ids=ids),
+                *fq.encode(x[:0], k, N, Rd, Cd)]
+
+    def refused():
+        p, n = fq.encode(x, k, N, Rd, Cd)
+        kv = (p.view(2, T, P), n.view(2, T), p.view(2, T, P), n.view(2, T))
+        bad = [lambda: fq.encode(x[:, ::2], k, N, Rd, Cd), lambda: fq.encode(x, k, N, Rd.t(), Cd),
+               lambda: fq.encode(x, k, N, Rd.cpu(), Cd), lambda: fq.encode(x, 3, N, Rd, Cd),
+               lambda: fq.encode(x, k, N, Rd, Cd[:128]), lambda: fq.encode(x, k, N, Rd, Cd, payload=p[:9]),
+               lambda: fq.decode(p, n[:7], d, k, N, Rd, Cd),
+               lambda: fq.decode(p, n, d, k, N, Rd, Cd, token_ids=ids.int()),
+               lambda: fq.attn_decode(q, *kv, T + 1, k, N, Rd, Cd),
+               lambda: fq.attn_decode(q, *kv, T, k, N, Rd, Cd, scale=float("nan")),
+               lambda: fq.attn_decode(q.to(torch.float64), *kv, T, k, N, Rd, Cd),
+               lambda: fq.attn_decode(q, *kv, T, k, N, Rd, Cd,
+                                      workspace=torch.empty(1, dtype=torch.uint8, device=device).cpu())]
+        said = []
+        for f in bad:
+            with pytest.raises((ValueError, fq.FibqError)) as e:
+                f()
+            said.append((type(e.value), str(e.value)))
+        return said
+
+    _say("[edge] compiled binding")
+    fq.lib()
+    assert fq._fast is not None
+    fast, fast_bad = calls(), refused()
+    monkeypatch.setattr(fq, "_fast", None)
+    slow, slow_bad = calls(), refused()
+    torch.cuda.synchronize()
+    for a, b in zip(fast, slow):
+        assert a.dtype == b.dtype and torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+    assert fast_bad == slow_bad
