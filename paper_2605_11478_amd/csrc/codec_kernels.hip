@@ -13,9 +13,8 @@
 //     ties) in every case;
 //   - the d/k indices are bit-packed into P bytes, staged in LDS and stored
 //     with coalesced dword writes; the fp16 header is a coalesced u16 store.
-// Decoder, d / 16 threads per output vector: unpack, gather codewords from
-// LDS, x_hat = nu Pi^T y_hat in float32 (Pi in LDS), 16 consecutive outputs
-// per thread stored as float4 (coalesced rows).
+// Decoder: unpack, gather codewords, x_hat = nu Pi^T y_hat in float32, on the
+// matrix cores or as a sum of table rows (see the kernels).
 #include <hip/hip_runtime.h>
 #include <atomic>
 
@@ -640,8 +639,54 @@ __global__ __launch_bounds__(kEncThreads) void encode_list_kernel(
   }
 }
 
-// D / 16 lanes per output row, each producing 16 consecutive floats, so a
-// wavefront's float4 stores cover whole contiguous rows.
+// Decoder, x_hat = nu Pi^T y_hat as a float32 matrix product: a wavefront takes
+// one or two tiles of 16 rows per step.  Lane group g (lanes 16 g .. 16 g + 15)
+// gathers quarter g of y_hat of row lane % 16 of a tile (the B operand of
+// v_mfma_f32_16x16x4_f32: K slot (s, g) is coordinate (D / 4) g + s), A is
+// Pi^T from LDS in operand order (16 bytes per lane and four products), and a
+// lane ends with four consecutive outputs of its row (16-byte stores).
+//
+// Bound: 16 rows are (D / 16)(D / 4) products of 32 clocks on a SIMD (147456
+// rows of d = 64: 8.4 us), beside the output's bytes.  On the vector units,
+// with Pi read from LDS for every row: DEC_NOTE.
+template <int D>
+constexpr int dec_tiles() { return D == 64 ? 2 : 1; }
+constexpr size_t kDecLds = 64 * 1024;  // codebooks up to here are staged beside Pi^T
+typedef float dec_f4 __attribute__((ext_vector_type(4)));
+
+// Indices m0 .. m0 + NI - 1 of a payload row of P bytes.
+template <int NI>
+__device__ __forceinline__ void row_indices(const uint8_t* p, int m0, int W, int P, uint32_t (&id)[NI]) {
+  const uint32_t mask = (1u << W) - 1u;
+  const int bit0 = m0 * W, nb = NI * W;  // nb, P: wave-uniform
+  if (P >= 4 && (nb <= 25 || nb == 32)) {
+    const int st = min(bit0 >> 3, P - 4);
+    uint32_t v;
+    __builtin_memcpy(&v, p + st, 4);
+    v >>= bit0 - 8 * st;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) id[i] = (i * W < 32 ? v >> (i * W) : 0u) & mask;
+  } else if (P >= 8 && (nb <= 57 || nb == 64)) {
+    const int st = min(bit0 >> 3, P - 8);
+    uint64_t v;
+    __builtin_memcpy(&v, p + st, 8);
+    v >>= bit0 - 8 * st;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) id[i] = (uint32_t)(i * W < 64 ? v >> (i * W) : 0u) & mask;
+  } else if (P >= 4) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int bit = bit0 + i * W, st = min(bit >> 3, P - 4);
+      uint32_t v;
+      __builtin_memcpy(&v, p + st, 4);
+      id[i] = (v >> (bit - 8 * st)) & mask;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) id[i] = extract_index(p, m0 + i, W);
+  }
+}
+
 template <int D, int K, bool CG>
 __global__ __launch_bounds__(256) void decode_kernel(const uint8_t* __restrict__ payload,
                                                      const uint16_t* __restrict__ norms,
@@ -650,63 +695,81 @@ __global__ __launch_bounds__(256) void decode_kernel(const uint8_t* __restrict__
                                                      const float* __restrict__ R,
                                                      const float* __restrict__ C, int N, int W,
                                                      int P, float* __restrict__ out) {
-  constexpr int NB = D / K;
-  constexpr int TPV = D / 16;  // lanes per row
+  constexpr int Q = D / 4;                      // coordinates of a lane's quarter
+  constexpr int NI = K <= Q ? Q / K : 1;        // its indices
+  constexpr int MT = D / 16, S4 = Q / 4, kDecTiles = dec_tiles<D>();
   extern __shared__ __align__(16) unsigned char smem[];
-  float* Rs = reinterpret_cast<float*>(smem);
-  float* Cs = Rs + D * D;
-  const float* Cb = CG ? C : Cs;  // large codebooks: gathered from global memory
-  for (int i = threadIdx.x; i < D * D; i += blockDim.x) Rs[i] = R[i];
+  dec_f4* pit = reinterpret_cast<dec_f4*>(smem);  // [MT][S4][64]
+  float* Cs = reinterpret_cast<float*>(pit + MT * S4 * 64);
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, n = lane & 15;
+  for (int i = tid; i < MT * S4 * 64; i += 256) {
+    const int l = i & 63, s4 = (i >> 6) % S4, mt = (i >> 6) / S4;
+    const float* r = R + (size_t)(Q * (l >> 4) + 4 * s4) * D + 16 * mt + (l & 15);
+    pit[i] = dec_f4{r[0], r[D], r[2 * D], r[3 * D]};
+  }
   if (!CG)
-    for (int i = threadIdx.x; i < N * K; i += blockDim.x) Cs[i] = C[i];
+    for (int i = tid; i < N * K; i += 256) Cs[i] = C[i];
   __syncthreads();
-  const int q = threadIdx.x % TPV;  // this lane's 16 dims: 16 q .. 16 q + 15
-  for (int64_t gv = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / TPV; gv < n_vec;
-       gv += (int64_t)gridDim.x * blockDim.x / TPV) {
-    const int64_t t = ids ? ids[gv] : gv;
-    float4* o = reinterpret_cast<float4*>(out + gv * D + 16 * q);
-    if (t < 0 || t >= n_cache) {
-      const float nan = __int_as_float(0x7FC00000);
+  const float* Cb = CG ? C : Cs;
+  const int64_t step = (int64_t)gridDim.x * 4 * kDecTiles * 16;
+  for (int64_t v0 = ((int64_t)blockIdx.x * 4 + (tid >> 6)) * kDecTiles * 16; v0 < n_vec; v0 += step) {
+    float y[kDecTiles][Q];
+    float h[kDecTiles];
+    int64_t row[kDecTiles];
+    bool ok[kDecTiles];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o[j] = make_float4(nan, nan, nan, nan);
-      continue;
-    }
-    const uint8_t* p = payload + t * (int64_t)P;
-    float yh[D];
+    for (int t = 0; t < kDecTiles; ++t) {
+      row[t] = v0 + 16 * t + n;
+      const int64_t rc = row[t] < n_vec ? row[t] : n_vec - 1;  // (ragged end)
+      const int64_t id = ids ? ids[rc] : rc;
+      ok[t] = id >= 0 && id < n_cache;
+      const int64_t c = ok[t] ? id : 0;
+      uint32_t ix[NI];
+      if (n_cache > 0) {
+        row_indices<NI>(payload + c * P, K <= Q ? g * NI : g * Q / K, W, P, ix);
+        h[t] = half_bits_to_float(norms[c]);
+      } else {
 #pragma unroll
-    for (int m = 0; m < NB; ++m) {
-      const uint32_t id = extract_index(p, m, W);
+        for (int i = 0; i < NI; ++i) ix[i] = 0;
+        h[t] = 0.0f;
+      }
 #pragma unroll
-      for (int r = 0; r < K; ++r) yh[m * K + r] = Cb[id * K + r];
-    }
-    const float h = half_bits_to_float(norms[t]);
-    float acc[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) acc[j] = 0.0f;
-    // (fully unrolled: a partly unrolled loop indexes y_hat at run time,
-    // which puts the array in scratch memory)
-#pragma unroll
-    for (int i = 0; i < D; ++i) {  // x_hat = nu Pi^T y_hat: row i of Pi times y_hat_i
-      const float4* row = reinterpret_cast<const float4*>(Rs + i * D + 16 * q);
-#pragma unroll
-      for (int j4 = 0; j4 < 4; ++j4) {
-        const float4 r4 = row[j4];
-        acc[4 * j4 + 0] = fmaf(r4.x, yh[i], acc[4 * j4 + 0]);
-        acc[4 * j4 + 1] = fmaf(r4.y, yh[i], acc[4 * j4 + 1]);
-        acc[4 * j4 + 2] = fmaf(r4.z, yh[i], acc[4 * j4 + 2]);
-        acc[4 * j4 + 3] = fmaf(r4.w, yh[i], acc[4 * j4 + 3]);
+      for (int i = 0; i < NI; ++i) {
+        constexpr int E = K <= Q ? K : Q;  // entries of the codeword in this quarter
+        const float* cw = Cb + (size_t)ix[i] * K + (K <= Q ? 0 : g * Q % K);
+        __builtin_memcpy(&y[t][i * E], cw, 4 * E);
       }
     }
+#pragma unroll 1
+    for (int mt = 0; mt < MT; ++mt) {
+      dec_f4 acc[kDecTiles] = {};
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      o[j] = make_float4(h * acc[4 * j], h * acc[4 * j + 1], h * acc[4 * j + 2], h * acc[4 * j + 3]);
+      for (int s4 = 0; s4 < S4; ++s4) {
+        const dec_f4 A = pit[(mt * S4 + s4) * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < kDecTiles; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[e], y[t][4 * s4 + e], acc[t], 0, 0, 0);
+      }
+#pragma unroll
+      for (int t = 0; t < kDecTiles; ++t) {
+        const float nan = __int_as_float(0x7FC00000);
+        const dec_f4 o = ok[t] ? acc[t] * h[t] : dec_f4{nan, nan, nan, nan};
+        if (row[t] < n_vec) *reinterpret_cast<dec_f4*>(out + row[t] * D + 16 * mt + 4 * g) = o;
+      }
+    }
   }
 }
 
 // Small codebooks (d/k * N * d floats <= 64 KB): x_hat = nu Pi^T y_hat is a sum
 // of d/k rows of the table T[m][j] = Pi_m^T c_j (Pi_m: the k rows of Pi of
 // block m), which each workgroup builds once in LDS; a row then costs d/k
-// gathers of its 16 dims per lane instead of the d x d product.
+// gathers of its 16 dims per lane.  D / 16 lanes per output row; in step j they
+// read 16-byte pieces side by side, and rows start at different j (a table row
+// is a multiple of all banks: in the same order every row of a wavefront would
+// hit the same ones; 65536 ids of the 32k cache TAB_NOTE).  Half the rounding
+// error of the product above, and faster for few rows.
 constexpr int kDecTab = 16384;  // floats
 
 template <int D, int K>
@@ -736,36 +799,46 @@ __global__ __launch_bounds__(256) void decode_table_kernel(const uint8_t* __rest
     }
   }
   __syncthreads();
-  const int q = threadIdx.x % TPV;
+  const int q = threadIdx.x % TPV, turn = threadIdx.x / TPV;
+  int at[4];  // this lane's dims: at[j] .. at[j] + 3
+#pragma unroll
+  for (int j = 0; j < 4; ++j) at[j] = 4 * q + 4 * TPV * ((j + turn) & 3);
   for (int64_t gv = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / TPV; gv < n_vec;
        gv += (int64_t)gridDim.x * blockDim.x / TPV) {
     const int64_t t = ids ? ids[gv] : gv;
-    float4* o = reinterpret_cast<float4*>(out + gv * D + 16 * q);
+    float* o = out + gv * D;
     if (t < 0 || t >= n_cache) {
       const float nan = __int_as_float(0x7FC00000);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o[j] = make_float4(nan, nan, nan, nan);
+      for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<float4*>(o + at[j]) = make_float4(nan, nan, nan, nan);
       continue;
     }
     const uint8_t* p = payload + t * (int64_t)P;
     float4 acc[4] = {};
-#pragma unroll 4
-    for (int m = 0; m < NB; ++m) {
-      const uint32_t id = extract_index(p, m, W);
-      const float4* tr = reinterpret_cast<const float4*>(tab + ((size_t)m * N + id) * D + 16 * q);
+    constexpr int NE = NB < 4 ? NB : 4;
+#pragma unroll 2
+    for (int m0 = 0; m0 < NB; m0 += NE) {
+      uint32_t id[NE];
+      row_indices<NE>(p, m0, W, P, id);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float4 v = tr[j];
-        acc[j].x += v.x;
-        acc[j].y += v.y;
-        acc[j].z += v.z;
-        acc[j].w += v.w;
+      for (int e = 0; e < NE; ++e) {
+        const float* tr = tab + ((size_t)(m0 + e) * N + id[e]) * D;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const float4 v = *reinterpret_cast<const float4*>(tr + at[j]);
+          acc[j].x += v.x;
+          acc[j].y += v.y;
+          acc[j].z += v.z;
+          acc[j].w += v.w;
+        }
       }
     }
     const float h = half_bits_to_float(norms[t]);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      o[j] = make_float4(h * acc[j].x, h * acc[j].y, h * acc[j].z, h * acc[j].w);
+      *reinterpret_cast<float4*>(o + at[j]) = make_float4(h * acc[j].x, h * acc[j].y,
+                                                          h * acc[j].z, h * acc[j].w);
   }
 }
 
@@ -988,16 +1061,19 @@ static int launch_decode_cg(const uint8_t* payload, const uint16_t* norms, const
                             const float* C, float* out, hipStream_t st) {
   const size_t lds = sizeof(float) * ((size_t)D * D + (CG ? 0 : (size_t)s.N * K));
   auto kern = decode_kernel<D, K, CG>;
-  hipError_t e = hipFuncSetAttribute((const void*)kern,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return (int)e;
-  const int64_t nb = (n_vec * (D / 16) + 255) / 256;
-  // every workgroup stages Pi (and a small codebook) in LDS: no more
-  // workgroups than fit on the compute units at once, so large stagings
-  // (d = 128 with 64 KB codebooks: 128 KB) are not repeated per batch of rows
-  const int64_t per_cu = (int64_t)(160 * 1024 / lds) < 8 ? (int64_t)(160 * 1024 / lds) : 8;
-  const int64_t cap = (int64_t)num_cus() * (per_cu > 0 ? per_cu : 1);
-  const int grid = (int)(nb < cap ? nb : cap);
+  if (lds > 65536) {  // above the default dynamic LDS limit
+    const hipError_t e = hipFuncSetAttribute(
+        (const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return (int)e;
+  }
+  const int64_t per = 4 * dec_tiles<D>() * 16, nb = (n_vec + per - 1) / per;
+  // every workgroup stages Pi^T (and a small codebook): no more workgroups
+  // than fit on the compute units at once
+  int64_t per_cu = (int64_t)(160 * 1024 / lds);
+  per_cu = per_cu < 1 ? 1 : (per_cu > 5 ? 5 : per_cu);
+  const int64_t cap = (int64_t)num_cus() * per_cu;
+  const int64_t rounds = (nb + cap - 1) / cap;
+  const int grid = (int)((nb + rounds - 1) / rounds);  // (equal rounds)
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, payload, norms, ids, n_vec, n_cache, R,
                      C, s.N, s.w, s.P, out);
   return (int)hipGetLastError();
@@ -1009,21 +1085,15 @@ static int launch_decode_t(const uint8_t* payload, const uint16_t* norms, const 
                            const float* C, float* out, hipStream_t st) {
   if ((int64_t)(D / K) * s.N * D <= kDecTab) {
     const size_t lds = sizeof(float) * (size_t)(D / K) * s.N * D;
-    auto kern = decode_table_kernel<D, K>;
-    hipError_t e = hipFuncSetAttribute((const void*)kern,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return (int)e;
     const int64_t nb = (n_vec * (D / 16) + 255) / 256;
     const int64_t cap = (int64_t)num_cus() * 4;  // the table is built once per workgroup
     const int grid = (int)(nb < cap ? nb : cap);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, payload, norms, ids, n_vec, n_cache,
-                       R, C, s.N, s.w, s.P, out);
+    hipLaunchKernelGGL((decode_table_kernel<D, K>), dim3(grid), dim3(256), lds, st, payload, norms,
+                       ids, n_vec, n_cache, R, C, s.N, s.w, s.P, out);
     return (int)hipGetLastError();
   }
-  // codebooks gathered from global memory (L2) when they do not fit beside Pi
-  // in a third of the LDS (d = 128 with 64 KB codebooks: two workgroups per
-  // compute unit instead of one)
-  if (s.N * K > kCbLds || (int64_t)(D * D + s.N * K) * 4 > 96 * 1024)
+  // codebooks that do not fit beside Pi^T are gathered from global memory (L2)
+  if ((size_t)s.N * K * 4 > (D == 64 ? kDecLds : kDecLds / 2))
     return launch_decode_cg<D, K, true>(payload, norms, ids, n_vec, n_cache, s, R, C, out, st);
   return launch_decode_cg<D, K, false>(payload, norms, ids, n_vec, n_cache, s, R, C, out, st);
 }

@@ -442,6 +442,43 @@ def test_encode_large_codebook_path(d, dtype, N, variant, device):
     assert torch.equal(p, p2) and torch.equal(nrm, n2)
 
 
+@pytest.mark.parametrize("d,k,N", [(64, 1, 4), (64, 1, 16), (64, 2, 2), (64, 2, 64), (64, 4, 16),
+                                   (64, 4, 256), (64, 4, 512), (64, 8, 4), (64, 8, 16),
+                                   (64, 8, 4096), (64, 16, 128), (64, 16, 8192), (64, 32, 256),
+                                   (64, 64, 8192), (128, 1, 16), (128, 2, 64), (128, 4, 4096),
+                                   (128, 8, 16), (128, 8, 512), (128, 16, 4096)])
+@pytest.mark.parametrize("n", [1, 31, 129, 2049])
+def test_decode_kernels(d, k, N, n, device):
+    """Both decoders (table rows, matrix product) at ragged tiles of 16 and 32
+    rows, index widths that straddle bytes and dwords, payload rows at odd
+    addresses, codebooks in LDS and in global memory, ids out of range between
+    others.  Bound: float32 sums of d products in any order, d 2^-24 |x| with
+    |x| = nu |y_hat| <= 1.2 nu here."""
+    R = oracle_rotation(d)
+    rng = np.random.default_rng(n + d + k + N)
+    C = rng.standard_normal((N, k)) * np.sqrt(1.0 / d)
+    C *= np.minimum(1.0, 1.2 * np.sqrt(k / d) / np.linalg.norm(C, axis=1, keepdims=True))
+    C = C.astype(np.float32)
+    idx = rng.integers(0, N, (n, d // k))
+    h = (np.abs(rng.standard_normal(n)) * 20).astype(np.float16)
+    pay = occ.pack(idx, N)
+    raw = torch.zeros(pay.size + 1, dtype=torch.uint8)
+    raw[1:] = torch.from_numpy(pay.reshape(-1))
+    pd = raw.to(device)[1:].view(n, -1)
+    nd = torch.from_numpy(occ.fp16_bits(h).view(np.int16)).to(device)
+    Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C).to(device)
+    _say(f"[edge] decode d={d} k={k} N={N} n={n}")
+    ref = occ.decode(idx, h, R.astype(np.float64), C.astype(np.float64))
+    tol = d * 2.0 ** -24 * 1.2 * np.maximum(h.astype(np.float64), 1e-30)[:, None]
+    out = fq.decode(pd, nd, d, k, N, Rd, Cd).cpu().numpy()
+    assert np.all(np.abs(out - ref) <= tol)
+    ids = rng.integers(0, n, n + 3)
+    ids[n // 2], ids[-1] = -1, n
+    got = fq.decode(pd, nd, d, k, N, Rd, Cd, token_ids=torch.from_numpy(ids).to(device)).cpu().numpy()
+    bad = (ids < 0) | (ids >= n)
+    assert np.isnan(got[bad]).all() and np.array_equal(got[~bad], out[ids[~bad]])
+
+
 @pytest.mark.parametrize("d,k,N,dtype,n,variant", [
     (64, 8, 2, torch.float32, 1, "plain"), (64, 8, 16, torch.float16, 17, "dup"),
     (64, 8, 32, torch.float32, 64, "fp16"), (64, 8, 64, torch.float16, 333, "strided"),
