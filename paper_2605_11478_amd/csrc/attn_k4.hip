@@ -46,6 +46,7 @@
 
 #include <type_traits>
 
+#include "attn_split.h"
 #include "device_common.h"
 #include "fibq.h"
 #include "fibq_internal.h"
@@ -70,27 +71,6 @@ typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-
-// The first unit of wavefront w of `waves`: w units / waves, from the quotient
-// and remainder of units by waves.  All of this is in 32 bits (units < 2^31,
-// waves < 2^16): a 64-bit division is 0.5 KB of code, and a small call's time
-// is mostly instruction fetches (a merge kernel of 50 KB took 34 us for 63
-// records, of 5 KB 4 us; this file's main kernel 14.4 us at 21 KB, 11.4 at 15).
-struct Split {
-  uint32_t units, q, r, waves, upg;
-};
-__host__ __device__ __forceinline__ uint32_t first_unit(uint32_t w, const Split& s) {
-  return w * s.q + w * s.r / s.waves;
-}
-
-// the wavefront whose unit range [first_unit(w), first_unit(w + 1)) holds u
-__device__ __forceinline__ uint32_t wave_of(uint32_t u, const Split& s) {
-  // (the float estimate is off by less than 0.1, and rounded down)
-  uint32_t w = (uint32_t)((float)u * ((float)s.waves / (float)s.units));
-  w = w > 0 ? w - 1 : 0;
-  while (first_unit(w + 1, s) <= u) ++w;
-  return w;
-}
 
 struct Plan {
   Split sp;       // 32-token units over all groups, their wavefronts
@@ -142,8 +122,7 @@ static Plan make_plan(int64_t n_groups, int64_t T, int D, int max_wgs) {
     p.pro = p.slots <= pro_groups(D);
   }
   const uint32_t waves = (uint32_t)(p.wgs * p.wpg);
-  p.sp = Split{(uint32_t)units, (uint32_t)(units / waves), (uint32_t)(units % waves), waves,
-               (uint32_t)p.upg};
+  p.sp = make_split(units, waves, p.upg);
   size_t off = 0;
   p.off_bq = off;
   if (!p.pro) off = al(off + (size_t)n_groups * (D / 32) * 64 * 8 * 2);

@@ -400,7 +400,7 @@ int launch_attn(const void* q, int q_dtype, const uint8_t* kp, const uint16_t* k
   // The 4-bit shape's own kernel where the groups are many: its one block per
   // group merges up to 256 / n_groups records (1 group of 131072 tokens 84 us,
   // 32 in attn_k4; 32 groups of 8192: 16.1 against 18.0).
-  if (attn_w4_applies(G, s) && n_groups >= 16 && T < (1LL << 30) && norms2)
+  if (attn_w4_applies(G, s) && n_groups >= 16 && attn_k4_fits(n_groups, T) && norms2)
     return launch_attn_w4(q, q_dtype, kp, kn, vp, vn, n_groups, T, T_stride, R, C, scale, out, ws,
                           st);
   // matrix-core kernel; the payload quarters of k <= 4 are read as aligned
@@ -409,7 +409,7 @@ int launch_attn(const void* q, int q_dtype, const uint8_t* kp, const uint16_t* k
       (s.k > 4 || ((reinterpret_cast<uintptr_t>(kp) | reinterpret_cast<uintptr_t>(vp)) & 3u) == 0))
     return launch_attn_k4(q, q_dtype, kp, kn, vp, vn, n_groups, G, T, T_stride, s, R, C, scale,
                           out, ws, st);
-  if (attn_w4_applies(G, s) && T < (1LL << 30) && norms2)
+  if (attn_w4_applies(G, s) && attn_k4_fits(n_groups, T) && norms2)
     return launch_attn_w4(q, q_dtype, kp, kn, vp, vn, n_groups, T, T_stride, R, C, scale, out, ws,
                           st);
 #define FIBQ_ATTN_CASE(DD, KK)                                                                 \

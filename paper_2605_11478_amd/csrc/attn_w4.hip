@@ -42,6 +42,7 @@
 
 #include <type_traits>
 
+#include "attn_split.h"
 #include "device_common.h"
 #include "fibq.h"
 #include "fibq_internal.h"
@@ -82,7 +83,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 struct Plan {
-  int64_t units;  // 64-token units over all groups
+  Split sp;       // units over all groups, their workgroups
   int upg;        // units per group
   int wgs, slots; // workgroups, records per workgroup
   size_t off_q, off_qs, off_cb, off_rec, total;
@@ -94,10 +95,11 @@ static Plan make_plan(int64_t n_groups, int64_t T) {
   Plan p{};
   p.upg = (int)((T + kUnit - 1) / kUnit);
   if (p.upg < 1) p.upg = 1;
-  p.units = n_groups * p.upg;
-  p.wgs = (int)(p.units < kMaxWgs ? p.units : kMaxWgs);
+  const int64_t units = n_groups * p.upg;
+  p.wgs = (int)(units < kMaxWgs ? units : kMaxWgs);
   if (p.wgs < 1) p.wgs = 1;
-  const int64_t upw = (p.units + p.wgs - 1) / p.wgs;
+  p.sp = make_split(units, p.wgs, p.upg);
+  const int64_t upw = (units + p.wgs - 1) / p.wgs;
   p.slots = (int)((upw + p.upg - 1) / p.upg + 1);
   size_t off = 0;
   p.off_q = off;
@@ -110,18 +112,6 @@ static Plan make_plan(int64_t n_groups, int64_t T) {
   off = al(off + (size_t)p.wgs * p.slots * kRec * 4);
   p.total = off;
   return p;
-}
-
-__host__ __device__ inline int64_t first_unit(int64_t w, int64_t units, int wgs) {
-  return (w * units) / wgs;
-}
-
-// workgroup whose unit range contains unit u
-__device__ inline int wg_of(int64_t u, int64_t units, int wgs) {
-  int64_t w = (u * wgs) / units;
-  while (w + 1 < wgs && first_unit(w + 1, units, wgs) <= u) ++w;
-  while (w > 0 && first_unit(w, units, wgs) > u) --w;
-  return (int)w;
 }
 
 // ----------------------------------------------------------------- prep ----
@@ -308,7 +298,7 @@ template <bool FUSED>
 __global__ __launch_bounds__(kThreads) void main_kernel(
     const uint8_t* __restrict__ kp, const uint16_t* __restrict__ kn,
     const uint8_t* __restrict__ vp, const uint16_t* __restrict__ vn, int T, int64_t T_stride,
-    int64_t units, int upg, int slots, int ring_ok, const _Float16* __restrict__ qop,
+    Split sp, int slots, int ring_ok, const _Float16* __restrict__ qop,
     const float* __restrict__ qsc, const _Float16* __restrict__ cbg, float* __restrict__ rec,
     Fused fz) {
   // LDS: the codebook tables first (their row offsets then need no base),
@@ -358,10 +348,10 @@ __global__ __launch_bounds__(kThreads) void main_kernel(
   }
   __syncthreads();
 
-  const int wgs = gridDim.x;
+  const int upg = sp.upg;
   const int64_t w = blockIdx.x;
-  const int64_t u0 = first_unit(w, units, wgs), u1 = first_unit(w + 1, units, wgs);
-  const int64_t g_first = u0 / upg, g_last = (u1 - 1) / upg;
+  const uint32_t u0 = first_unit(blockIdx.x, sp), u1 = first_unit(blockIdx.x + 1, sp);
+  const int64_t g_first = u0 / sp.upg, g_last = (u1 - 1) / sp.upg;
   const unsigned char* cbb = reinterpret_cast<const unsigned char*>(cb);
   const unsigned char* cbl = cbb + NC * K * 2;
   unsigned char* wb = smem + kOffW + wave * 2 * kWBuf;
@@ -386,7 +376,7 @@ __global__ __launch_bounds__(kThreads) void main_kernel(
   // claims: positions relative to the first unit of group g_first; the
   // group of the latest claim (index ck relative to g_first, first position
   // cbase, first token row crow) is tracked incrementally
-  const int pos0 = (int)(u0 - g_first * upg);
+  const int pos0 = (int)(u0 - (uint32_t)g_first * sp.upg);
   const int n_w = (int)(u1 - u0);
   int ck = 0, cbase = 0;
   int64_t crow = g_first * T_stride;
@@ -874,71 +864,63 @@ constexpr int kMergeThreads = 256;
 constexpr int kMergeMax = 4;   // contributors per pass over the records
 
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const float* __restrict__ rec,
-                                                              int64_t units, int upg, int wgs,
-                                                              int slots,
+                                                              Split sp, int slots,
                                                               const float* __restrict__ R,
                                                               float* __restrict__ out) {
-  __shared__ __align__(16) float rs[D * D];  // Pi row-major: column reads are conflict-free
-  __shared__ __align__(16) float ra[G * D];
+  // block (group, four heads); thread: head h0 + tid / 64, dim j; then o = Pi^T a
+  // with Pi's rows in four stripes over the wavefronts
+  constexpr int HB = 4, RI = D / HB;
+  __shared__ float ra[HB * D];
+  __shared__ float part[HB][HB * D];
   const int64_t g = blockIdx.x;
-  const int tid = threadIdx.x, j = tid & (D - 1), h0 = tid >> 6, h1 = h0 + 4;
-  float4 r4[D * D / 4 / kMergeThreads];
+  const int tid = threadIdx.x, j = tid & (D - 1), st = tid >> 6, h = HB * blockIdx.y + st;
+  float pi[RI];
 #pragma unroll
-  for (int e = 0; e < D * D / 4 / kMergeThreads; ++e)
-    r4[e] = reinterpret_cast<const float4*>(R)[tid + e * kMergeThreads];
-  const int wlo = wg_of(g * upg, units, wgs), whi = wg_of((g + 1) * upg - 1, units, wgs);
-  float M0 = -INFINITY, L0 = 0.0f, a0 = 0.0f, M1 = -INFINITY, L1 = 0.0f, a1 = 0.0f;
+  for (int i = 0; i < RI; ++i) pi[i] = R[(st * RI + i) * D + j];
+  const uint32_t first = (uint32_t)g * sp.upg;
+  const int wlo = (int)wave_of(first, sp), whi = (int)wave_of(first + sp.upg - 1, sp);
+  float M = -INFINITY, L = 0.0f, a = 0.0f;
   for (int base = wlo; base <= whi; base += kMergeMax) {
-    float m0[kMergeMax], l0[kMergeMax], x0[kMergeMax], m1[kMergeMax], l1[kMergeMax],
-        x1[kMergeMax];
+    float mk[kMergeMax], lk[kMergeMax], xk[kMergeMax];
 #pragma unroll
     for (int k = 0; k < kMergeMax; ++k) {
-      const int ww = base + k;
-      if (ww <= whi) {
-        const int64_t fg = first_unit(ww, units, wgs) / upg;
-        const float* rr = rec + ((int64_t)ww * slots + (g - fg)) * kRec;
-        m0[k] = rr[h0]; l0[k] = rr[G + h0]; x0[k] = rr[2 * G + h0 * D + j];
-        m1[k] = rr[h1]; l1[k] = rr[G + h1]; x1[k] = rr[2 * G + h1 * D + j];
-      } else {
-        m0[k] = m1[k] = -INFINITY;
-        l0[k] = l1[k] = x0[k] = x1[k] = 0.0f;
-      }
+      const int w = min(base + k, whi);
+      const uint32_t fg = first_unit(w, sp) / sp.upg;
+      const float* rr = rec + ((int64_t)w * slots + ((uint32_t)g - fg)) * kRec;
+      const bool has = base + k <= whi;
+      mk[k] = has ? rr[h] : -INFINITY;
+      lk[k] = has ? rr[G + h] : 0.0f;
+      xk[k] = has ? rr[2 * G + h * D + j] : 0.0f;
     }
-    auto fold = [&](float& M, float& L, float& a, const float* mk, const float* lk,
-                    const float* xk) {
-      float Mn = M;
+    float Mn = M;
 #pragma unroll
-      for (int k = 0; k < kMergeMax; ++k) Mn = fmaxf(Mn, mk[k]);
-      if (Mn == -INFINITY) return;
-      const float fo = (M == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(M - Mn);
-      L *= fo;
-      a *= fo;
+    for (int k = 0; k < kMergeMax; ++k) Mn = fmaxf(Mn, mk[k]);
+    if (Mn == -INFINITY) continue;
+    const float fo = __builtin_amdgcn_exp2f(M - Mn);  // exp2(-inf) = 0
+    L *= fo;
+    a *= fo;
 #pragma unroll
-      for (int k = 0; k < kMergeMax; ++k) {
-        const float f = (mk[k] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f(mk[k] - Mn);
-        L = fmaf(lk[k], f, L);
-        a = fmaf(xk[k], f, a);
-      }
-      M = Mn;
-    };
-    fold(M0, L0, a0, m0, l0, x0);
-    fold(M1, L1, a1, m1, l1, x1);
+    for (int k = 0; k < kMergeMax; ++k) {
+      const float f = __builtin_amdgcn_exp2f(mk[k] - Mn);
+      L = fmaf(lk[k], f, L);
+      a = fmaf(xk[k], f, a);
+    }
+    M = Mn;
   }
-#pragma unroll
-  for (int e = 0; e < D * D / 4 / kMergeThreads; ++e)
-    reinterpret_cast<float4*>(rs)[tid + e * kMergeThreads] = r4[e];
-  ra[h0 * D + j] = (L0 > 0.0f) ? a0 / L0 : 0.0f;
-  ra[h1 * D + j] = (L1 > 0.0f) ? a1 / L1 : 0.0f;
+  ra[st * D + j] = (L > 0.0f) ? a / L : 0.0f;
   __syncthreads();
-  float o0 = 0.0f, o1 = 0.0f;  // o[h][j] = sum_i Pi[i][j] a[h][i]
-#pragma unroll 16
-  for (int i = 0; i < D; ++i) {
-    const float r = rs[i * D + j];
-    o0 = fmaf(r, ra[h0 * D + i], o0);
-    o1 = fmaf(r, ra[h1 * D + i], o1);
+#pragma unroll
+  for (int x = 0; x < HB; ++x) {
+    float o = 0.0f;
+#pragma unroll
+    for (int i = 0; i < RI; ++i) o = fmaf(pi[i], ra[x * D + st * RI + i], o);
+    part[st][x * D + j] = o;
   }
-  out[g * G * D + h0 * D + j] = o0;
-  out[g * G * D + h1 * D + j] = o1;
+  __syncthreads();
+  float o = 0.0f;
+#pragma unroll
+  for (int x = 0; x < HB; ++x) o += part[x][tid];
+  out[g * G * D + HB * blockIdx.y * D + tid] = o;
 }
 
 }  // namespace w4
@@ -972,7 +954,7 @@ int launch_attn_w4(const void* q, int q_dtype, const uint8_t* kp, const uint16_t
   if (T > 0 && p.slots <= w4::kFusedGroups) {
     // the main kernel prepares its own groups' query operands
     hipLaunchKernelGGL(w4::main_kernel<true>, dim3((unsigned)p.wgs), dim3(w4::kThreads), 0, st, kp,
-                       kn, vp, vn, (int)T, T_stride, p.units, p.upg, p.slots, ring_ok, qop, qsc,
+                       kn, vp, vn, (int)T, T_stride, p.sp, p.slots, ring_ok, qop, qsc,
                        cb, rec, fz);
   } else {
     hipLaunchKernelGGL(w4::prep_kernel, dim3((unsigned)n_groups), dim3(256), 0, st, q, q_dtype, R,
@@ -980,13 +962,13 @@ int launch_attn_w4(const void* q, int q_dtype, const uint8_t* kp, const uint16_t
     e = hipGetLastError();
     if (e != hipSuccess || T == 0) return (int)e;
     hipLaunchKernelGGL(w4::main_kernel<false>, dim3((unsigned)p.wgs), dim3(w4::kThreads), 0, st,
-                       kp, kn, vp, vn, (int)T, T_stride, p.units, p.upg, p.slots, ring_ok, qop,
+                       kp, kn, vp, vn, (int)T, T_stride, p.sp, p.slots, ring_ok, qop,
                        qsc, cb, rec, fz);
   }
   e = hipGetLastError();
   if (e != hipSuccess) return (int)e;
-  hipLaunchKernelGGL(w4::merge_kernel, dim3((unsigned)n_groups), dim3(w4::kMergeThreads), 0, st,
-                     rec, p.units, p.upg, p.wgs, p.slots, R, out);
+  hipLaunchKernelGGL(w4::merge_kernel, dim3((unsigned)n_groups, w4::G / 4),
+                     dim3(w4::kMergeThreads), 0, st, rec, p.sp, p.slots, R, out);
   return (int)hipGetLastError();
 }
 
