@@ -96,7 +96,7 @@ def _bind(L):
     from . import _binding
     _binding.bind(*(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in
                     ("fibq_encode", "fibq_decode", "fibq_attn_decode",
-                     "fibq_attn_workspace_bytes", "fibq_payload_bytes")))
+                     "fibq_attn_workspace_bytes", "fibq_payload_bytes")), _check)
     _fast = _binding
 
 

@@ -3,7 +3,8 @@
 // interpreter between them (14 us of checks around a 7 us kernel before, about
 // 2 us here).  Every function returns None, having done nothing, for any
 // argument that it does not recognise as valid; the Python code then goes
-// through its own checks, which name what is wrong.
+// through its own checks, which name what is wrong.  Once the library has been
+// entered, its status is final: anything but FIBQ_OK raises FibqError.
 //
 // The library is reached through the entry points that bind() is given (the
 // loaded library's own), so this module does not load it.
@@ -25,6 +26,7 @@ decltype(&fibq_decode) g_decode;
 decltype(&fibq_attn_decode) g_attn;
 decltype(&fibq_attn_workspace_bytes) g_ws;
 decltype(&fibq_payload_bytes) g_payload;
+PyObject* g_check;  // the package's _check(status, where): raises FibqError
 
 using at::Tensor;
 
@@ -75,6 +77,17 @@ bool codec(const Tensor* R, const Tensor* C, int64_t d, int64_t k, int64_t N, at
   return *P > 0;
 }
 
+// Raises FibqError for a status of the library.  (Not None: the Python code
+// would enter the library a second time, and a HIP error is reported once.)
+PyObject* raise_status(int rc, const char* where) {
+  PyObject* r = PyObject_CallFunction(g_check, "is", rc, where);
+  if (r) {  // (_check returned)
+    Py_DECREF(r);
+    PyErr_SetString(PyExc_RuntimeError, where);
+  }
+  return nullptr;
+}
+
 #define FIBQ_NONE return Py_NewRef_(Py_None)
 PyObject* Py_NewRef_(PyObject* o) {
   Py_INCREF(o);
@@ -115,7 +128,7 @@ PyObject* encode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
                           static_cast<const float*>(ptr(*R)), static_cast<const float*>(ptr(*C)),
                           static_cast<uint8_t*>(payload.data_ptr()),
                           static_cast<uint16_t*>(norms.data_ptr()), reinterpret_cast<void*>(st));
-  if (rc != FIBQ_OK) FIBQ_NONE;
+  if (rc != FIBQ_OK) return raise_status(rc, "fibq_encode");
   PyObject* r = PyTuple_New(2);
   if (!r) return nullptr;
   PyTuple_SET_ITEM(r, 0, keep(a[5], payload));
@@ -161,7 +174,7 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
                           ids, n, cache, (int)d, (int)k, rate, (int)N,
                           static_cast<const float*>(ptr(*R)), static_cast<const float*>(ptr(*C)),
                           static_cast<float*>(out.data_ptr()), reinterpret_cast<void*>(st));
-  if (rc != FIBQ_OK) FIBQ_NONE;
+  if (rc != FIBQ_OK) return raise_status(rc, "fibq_decode");
   return keep(a[8], out);
   END_HANDLE_TH_ERRORS
 }
@@ -213,16 +226,16 @@ PyObject* attn(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
                         static_cast<const float*>(ptr(*C)), (float)PyFloat_AS_DOUBLE(a[10]),
                         static_cast<float*>(out.data_ptr()), ws.data_ptr(), (size_t)ws.numel(),
                         reinterpret_cast<void*>(st));
-  if (rc != FIBQ_OK) FIBQ_NONE;
+  if (rc != FIBQ_OK) return raise_status(rc, "fibq_attn_decode");
   return keep(a[12], out);
   END_HANDLE_TH_ERRORS
 }
 
-// bind(encode, decode, attn_decode, attn_workspace_bytes, payload_bytes):
-// addresses of the loaded library's entry points
+// bind(encode, decode, attn_decode, attn_workspace_bytes, payload_bytes,
+// check): addresses of the loaded library's entry points, and _check
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
-  if (n_args != 5) {
-    PyErr_SetString(PyExc_TypeError, "bind takes five addresses");
+  if (n_args != 6) {
+    PyErr_SetString(PyExc_TypeError, "bind takes five addresses and a callable");
     return nullptr;
   }
   void* p[5];
@@ -235,6 +248,8 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   g_attn = reinterpret_cast<decltype(g_attn)>(p[2]);
   g_ws = reinterpret_cast<decltype(g_ws)>(p[3]);
   g_payload = reinterpret_cast<decltype(g_payload)>(p[4]);
+  Py_INCREF(a[5]);
+  Py_XSETREF(g_check, a[5]);
   Py_RETURN_NONE;
 }
 
