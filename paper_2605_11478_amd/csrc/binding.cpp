@@ -88,6 +88,14 @@ PyObject* raise_status(int rc, const char* where) {
   return nullptr;
 }
 
+// Other Python threads run while this lives: an allocation may wait for the
+// allocator, and a launch for a free place in the queue or, the first time,
+// for the kernels to be loaded.  Raw pointers are taken before.
+struct NoGil {
+  PyThreadState* state = PyEval_SaveThread();
+  ~NoGil() { PyEval_RestoreThread(state); }
+};
+
 #define FIBQ_NONE return Py_NewRef_(Py_None)
 PyObject* Py_NewRef_(PyObject* o) {
   Py_INCREF(o);
@@ -122,12 +130,18 @@ PyObject* encode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     norms = *t;
   }
   const auto opt = at::TensorOptions().device(x->device());
-  if (!payload.defined()) payload = at::empty({n, P}, opt.dtype(at::kByte));
-  if (!norms.defined()) norms = at::empty({n}, opt.dtype(at::kShort));
-  const int rc = g_encode(ptr(*x), dt, n, x->stride(0), (int)d, (int)k, rate, (int)N,
-                          static_cast<const float*>(ptr(*R)), static_cast<const float*>(ptr(*C)),
-                          static_cast<uint8_t*>(payload.data_ptr()),
-                          static_cast<uint16_t*>(norms.data_ptr()), reinterpret_cast<void*>(st));
+  const void* px = ptr(*x);
+  const int64_t stride = x->stride(0);
+  const float *pR = static_cast<const float*>(ptr(*R)), *pC = static_cast<const float*>(ptr(*C));
+  int rc;
+  {
+    NoGil no_gil;
+    if (!payload.defined()) payload = at::empty({n, P}, opt.dtype(at::kByte));
+    if (!norms.defined()) norms = at::empty({n}, opt.dtype(at::kShort));
+    rc = g_encode(px, dt, n, stride, (int)d, (int)k, rate, (int)N, pR, pC,
+                  static_cast<uint8_t*>(payload.data_ptr()),
+                  static_cast<uint16_t*>(norms.data_ptr()), reinterpret_cast<void*>(st));
+  }
   if (rc != FIBQ_OK) return raise_status(rc, "fibq_encode");
   PyObject* r = PyTuple_New(2);
   if (!r) return nullptr;
@@ -167,13 +181,17 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     const Tensor* t = tensor(a[8]);
     if (!shaped(t, at::kFloat, {n, d}) || t->device() != dev) FIBQ_NONE;
     out = *t;
-  } else {
-    out = at::empty({n, d}, at::TensorOptions().device(dev).dtype(at::kFloat));
   }
-  const int rc = g_decode(static_cast<const uint8_t*>(ptr(*p)), static_cast<const uint16_t*>(ptr(*h)),
-                          ids, n, cache, (int)d, (int)k, rate, (int)N,
-                          static_cast<const float*>(ptr(*R)), static_cast<const float*>(ptr(*C)),
-                          static_cast<float*>(out.data_ptr()), reinterpret_cast<void*>(st));
+  const uint8_t* pp = static_cast<const uint8_t*>(ptr(*p));
+  const uint16_t* ph = static_cast<const uint16_t*>(ptr(*h));
+  const float *pR = static_cast<const float*>(ptr(*R)), *pC = static_cast<const float*>(ptr(*C));
+  int rc;
+  {
+    NoGil no_gil;
+    if (!out.defined()) out = at::empty({n, d}, at::TensorOptions().device(dev).dtype(at::kFloat));
+    rc = g_decode(pp, ph, ids, n, cache, (int)d, (int)k, rate, (int)N, pR, pC,
+                  static_cast<float*>(out.data_ptr()), reinterpret_cast<void*>(st));
+  }
   if (rc != FIBQ_OK) return raise_status(rc, "fibq_decode");
   return keep(a[8], out);
   END_HANDLE_TH_ERRORS
@@ -217,15 +235,20 @@ PyObject* attn(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     if (!shaped(t, at::kFloat, {ng, G, d}) || t->device() != dev) FIBQ_NONE;
     out = *t;
   }
-  if (!ws.defined()) ws = at::empty({need > 1 ? need : 1}, opt.dtype(at::kByte));
-  if (!out.defined()) out = at::empty({ng, G, d}, opt.dtype(at::kFloat));
-  const int rc = g_attn(ptr(*q), dt, static_cast<const uint8_t*>(ptr(*kp)),
-                        static_cast<const uint16_t*>(ptr(*kn)), static_cast<const uint8_t*>(ptr(*vp)),
-                        static_cast<const uint16_t*>(ptr(*vn)), ng, (int)G, T, Ts, (int)d, (int)k,
-                        rate, (int)N, static_cast<const float*>(ptr(*R)),
-                        static_cast<const float*>(ptr(*C)), (float)PyFloat_AS_DOUBLE(a[10]),
-                        static_cast<float*>(out.data_ptr()), ws.data_ptr(), (size_t)ws.numel(),
-                        reinterpret_cast<void*>(st));
+  const void* pq = ptr(*q);
+  const uint8_t *pkp = static_cast<const uint8_t*>(ptr(*kp)), *pvp = static_cast<const uint8_t*>(ptr(*vp));
+  const uint16_t *pkn = static_cast<const uint16_t*>(ptr(*kn)), *pvn = static_cast<const uint16_t*>(ptr(*vn));
+  const float *pR = static_cast<const float*>(ptr(*R)), *pC = static_cast<const float*>(ptr(*C));
+  const float scale = (float)PyFloat_AS_DOUBLE(a[10]);
+  int rc;
+  {
+    NoGil no_gil;
+    if (!ws.defined()) ws = at::empty({need > 1 ? need : 1}, opt.dtype(at::kByte));
+    if (!out.defined()) out = at::empty({ng, G, d}, opt.dtype(at::kFloat));
+    rc = g_attn(pq, dt, pkp, pkn, pvp, pvn, ng, (int)G, T, Ts, (int)d, (int)k, rate, (int)N, pR, pC,
+                scale, static_cast<float*>(out.data_ptr()), ws.data_ptr(), (size_t)ws.numel(),
+                reinterpret_cast<void*>(st));
+  }
   if (rc != FIBQ_OK) return raise_status(rc, "fibq_attn_decode");
   return keep(a[12], out);
   END_HANDLE_TH_ERRORS

@@ -97,3 +97,42 @@ def test_library_status_is_raised_and_not_retried():
         call()
         assert len(entered) == 2, (name, entered)
     ''')
+
+
+def test_other_threads_run_during_a_library_call(tmp_path):
+    """The library is entered without the interpreter lock: each stand-in (C)
+    waits until another Python thread has set a flag, 10 s at most, and
+    returns an error if none did."""
+    src, so = tmp_path / "wait.c", tmp_path / "wait.so"
+    src.write_text("""
+#include <unistd.h>
+volatile int entered, flag;
+int wait_for_flag(void) {
+  entered = 1;
+  for (int i = 0; i < 10000 && !flag; ++i) usleep(1000);
+  const int seen = flag;
+  entered = flag = 0;
+  return seen ? 0 : -3;
+}
+""")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", str(src), "-o", str(so)], check=True)
+    _child('''
+    W = ctypes.CDLL(sys.argv[1])
+    entered, flag = ctypes.c_int.in_dll(W, "entered"), ctypes.c_int.in_dll(W, "flag")
+    done = False
+    def other():
+        while not done:
+            if entered.value and not flag.value:
+                flag.value = 1
+            time.sleep(0.001)
+    t = threading.Thread(target=other)
+    t.start()
+    try:
+        for name, call in CALLS.items():
+            fq._lib = Library(**{name: W.wait_for_flag})
+            fq._bind(fq._lib)
+            call()
+    finally:
+        done = True
+        t.join()
+    ''', str(so))
