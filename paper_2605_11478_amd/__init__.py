@@ -1,8 +1,11 @@
 """FibQuant random-access KV-cache codec on MI355X (gfx950).
 
-Thin binding over ``libfibq.so`` (declared in ``include/fibq.h``; ctypes, and a
-compiled module for the calls on the decode path): argument marshalling only.  Every step of the codec runs in the library's HIP
-kernels; there is no CPU fallback, and a missing library raises.
+Thin binding over ``libfibq.so`` (declared in ``include/fibq.h``): argument
+marshalling only, by ctypes and, for encode, decode and attention calls on
+device tensors, by the compiled module ``_binding.so``, which the first such
+call loads (host functions need neither it nor torch).  Every step of the codec
+runs in the library's HIP kernels; there is no CPU fallback, and a missing
+library or module raises.
 
 Tensors passed to device functions must be CUDA (HIP) tensors, contiguous,
 on the current device; work is enqueued on torch's current stream.
@@ -27,7 +30,8 @@ F32, F16, BF16 = 0, 1, 2
 BINDING_PATH = os.path.join(_HERE, "_binding.so")
 
 _lib = None
-_fast = None  # the compiled binding, bound to the loaded library (see lib)
+_fast = None  # the compiled binding, once bound to the loaded library (see _bind)
+_bound = False
 
 
 class FibqError(RuntimeError):
@@ -80,15 +84,15 @@ def lib():
             fn.restype = res
             fn.argtypes = args
         _lib = L
-        _bind(L)
     return _lib
 
 
 def _bind(L):
     """Give the compiled per-call path (csrc/binding.cpp) the library's entry
     points.  It takes calls on device tensors that pass all checks and returns
-    None for any other, which the Python code below then checks and reports."""
-    global _fast
+    None for any other, which the Python code below then checks and reports.
+    Raises on every call until it succeeds; binding twice does no harm."""
+    global _fast, _bound
     if not os.path.exists(BINDING_PATH):
         raise ImportError(
             f"{BINDING_PATH} is missing: build it with `python -m paper_2605_11478_amd.build`")
@@ -98,6 +102,7 @@ def _bind(L):
                     ("fibq_encode", "fibq_decode", "fibq_attn_decode",
                      "fibq_attn_workspace_bytes", "fibq_payload_bytes")), _check)
     _fast = _binding
+    _bound = True
 
 
 def _raw_stream():
@@ -275,10 +280,13 @@ def _check_x(x):
 
 def encode(x, k, N, R, C, payload=None, norms=None):
     """x [n, d] (rows may be strided) -> (payload uint8 [n, P], norm bits int16 [n])."""
-    if _fast is not None and getattr(x, "is_cuda", False):
-        done = _fast.encode(x, k, N, R, C, payload, norms, _raw_stream())
-        if done is not None:
-            return done
+    if getattr(x, "is_cuda", False):
+        if not _bound:
+            _bind(lib())
+        if _fast is not None:
+            done = _fast.encode(x, k, N, R, C, payload, norms, _raw_stream())
+            if done is not None:
+                return done
     _check_x(x)
     n, d = x.shape
     _check_rc(R, C, d, k, N)
@@ -345,10 +353,13 @@ def encode_list(x, k, N, L, K, T, mu, offsets, members, R, C, payload=None, norm
 
 def decode(payload, norms, d, k, N, R, C, token_ids=None, out=None):
     """-> x_hat float32 [n, d]; rows token_ids (int64, device) or all rows."""
-    if _fast is not None and getattr(payload, "is_cuda", False):
-        done = _fast.decode(payload, norms, d, k, N, R, C, token_ids, out, _raw_stream())
-        if done is not None:
-            return done
+    if getattr(payload, "is_cuda", False):
+        if not _bound:
+            _bind(lib())
+        if _fast is not None:
+            done = _fast.decode(payload, norms, d, k, N, R, C, token_ids, out, _raw_stream())
+            if done is not None:
+                return done
     torch = _torch()
     P = payload_bytes(d, k, N)
     _want(payload, "payload", (torch.uint8,), (None, P))
@@ -402,11 +413,14 @@ def attn_decode(q, k_payload, k_norms, v_payload, v_norms, T, k, N, R, C, scale=
     ``attn_workspace_bytes`` bytes) may be reused across calls that do not
     overlap in time; a fresh one is allocated when omitted.
     """
-    if _fast is not None and getattr(q, "is_cuda", False):
-        done = _fast.attn(q, k_payload, k_norms, v_payload, v_norms, T, k, N, R, C, scale,
-                          workspace, out, _raw_stream())
-        if done is not None:
-            return done
+    if getattr(q, "is_cuda", False):
+        if not _bound:
+            _bind(lib())
+        if _fast is not None:
+            done = _fast.attn(q, k_payload, k_norms, v_payload, v_norms, T, k, N, R, C, scale,
+                              workspace, out, _raw_stream())
+            if done is not None:
+                return done
     torch = _torch()
     n_groups, G, d, T_stride, P, out = _check_attn(q, k_payload, k_norms, v_payload, v_norms,
                                                    T, k, N, R, C, out)

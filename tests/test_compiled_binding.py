@@ -136,3 +136,46 @@ int wait_for_flag(void) {
         done = True
         t.join()
     ''', str(so))
+
+
+def test_host_functions_need_neither_torch_nor_the_compiled_module():
+    """Building and loading codes works where torch cannot be imported and the
+    compiled module is not there."""
+    code = """
+import sys
+sys.modules["torch"] = None
+import paper_2605_11478_amd as fq
+fq.BINDING_PATH += ".absent"
+assert fq.build_rotation(64, 3).shape == (64, 64) and fq.payload_bytes(64, 8, 16) == 4
+assert fq.build_codebook(64, 4, 16, 1, M=2000, restarts=1, iters=1)[0].shape == (16, 4)
+try:
+    fq.load_codebook("/nowhere/at/all")
+except fq.FibqError as e:
+    assert e.status == fq.FIBQ_EIO
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_missing_compiled_module_raises_on_every_device_call():
+    """Never a silent second-best path: without the module every encode,
+    decode and attention call on device tensors raises ImportError."""
+    _child('''
+    path, fq.BINDING_PATH = fq.BINDING_PATH, fq.BINDING_PATH + ".absent"
+    for _ in range(2):
+        for name, call in CALLS.items():
+            try:
+                call()
+            except ImportError as e:
+                assert "missing" in str(e)
+            else:
+                raise AssertionError(f"{name} went on without the compiled module")
+    fq.BINDING_PATH = path
+    entered = []
+    entry = lambda *a: entered.append(1) or fq.FIBQ_OK
+    fq._lib = Library(**{n: ctypes.CFUNCTYPE(getattr(real, n).restype, *getattr(real, n).argtypes)(entry)
+                         for n in CALLS})
+    for name, call in CALLS.items():
+        call()
+    assert len(entered) == 3 and fq._fast is not None
+    ''')
