@@ -7,8 +7,8 @@
 // Block dimension k = 2 with w = 4 or 6 bits (N = 16 or 64) runs through the
 // same kernels: its payload, read as a stream of 2w-bit indices, is exactly
 // the payload of a k = 4 code over the pair codebook whose row i + N j is
-// (c_i, c_j) (index i of block 2p sits in the low w bits of pair p).  The
-// prep kernel writes that N^2-row table instead of the codebook.
+// (c_i, c_j) (index i of block 2p sits in the low w bits of pair p).  The main
+// kernel stages that N^2-row table instead of the codebook.
 //
 // Per wavefront, 32 cached tokens per step (two 16-token tiles):
 //   loads   the payload of a token is read as four contiguous quarters of
@@ -57,13 +57,13 @@ namespace k4 {
 
 constexpr int K = 4;
 constexpr int kMaxG = 8;
-constexpr int kMaxN = 4096;
 constexpr int kWaves = 8;       // wavefronts per workgroup, split plans
 constexpr int kWavesWhole = 16;  // one workgroup per group: as many as registers allow
 constexpr int whole_waves(int D) { return D == 64 ? kWavesWhole : kWaves; }
 constexpr int kMaxWgs = 512;     // split plans: two workgroups per compute unit
 constexpr int kStep = 32;        // tokens per unit
 constexpr int kHeadBlocks = 2048;  // merge: a block per head up to so many heads
+constexpr float kCs = 4096.0f;   // scale of the codebook's binary16 rows
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
@@ -324,6 +324,8 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
   extern __shared__ __align__(16) unsigned char smem[];  // rows hi [N KB][4], lo [N KB][4]; states
   __shared__ float qss[4];                               // query divisors of this workgroup's groups
   __shared__ int lastg[kWavesWhole];                     // last group of each wavefront, relative
+  __shared__ float cmax[kWavesWhole];                    // each wavefront's largest codebook entry,
+  __shared__ int clo[kWavesWhole];                       // whether it met a residual
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nthr = blockDim.x;
   const int wpg = nthr >> 6;
   const int g16 = lane >> 4, c = lane & 15;
@@ -414,37 +416,65 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
   // the first unit's loads go out before the codebook and the query are built
   Unit<QW> cur{};
   if (some) cur = load(g_first, step0);
-  // ---- binary16 rows of the codebook (k = 2: of the pair codebook, whose row
-  //      j holds codewords j % pair_n and j / pair_n) and their residuals
-  bool lo_any = false;
-  for (int i = tid; i < nrow; i += nthr) {
-    float cv[4];
-    if (pair_n > 0) {
-      __builtin_memcpy(cv, C + 2 * (i % pair_n), 8);
-      __builtin_memcpy(cv + 2, C + 2 * (i / pair_n), 8);
-    } else {
-      __builtin_memcpy(cv, C + (size_t)i * 4, 16);
-    }
-    h4 hi, lo;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      hi[e] = (_Float16)cv[e];
-      lo[e] = (_Float16)(cv[e] - (float)hi[e]);
-      lo_any |= (float)lo[e] != 0.0f;
-    }
-    reinterpret_cast<h4*>(smem)[i] = hi;
-    reinterpret_cast<h4*>(smem)[nrow + i] = lo;
-  }
+  // ---- binary16 rows of the codebook times cs (k = 2: of the pair codebook,
+  //      whose row j holds codewords j % pair_n and j / pair_n) and their
+  //      residuals.  Rows of unit vectors' blocks have entries up to 1; times
+  //      2^12 an entry above 2^-14 keeps 22 bits or more (unscaled, the residual
+  //      of one below 1/8 is a subnormal number, and a float32 codebook's
+  //      results were up to 1.5 times as far from float64 as the general
+  //      kernels').  Codebooks outside that range are staged once more, with
+  //      the power of two that takes their largest entry to [2^13, 2^14).
   const unsigned char* cbhi = smem;
   const unsigned char* cblo = smem + (size_t)nrow * 8;
   _Float16* bqs = reinterpret_cast<_Float16*>(smem + lds_qry);  // [slots][KS * 512]
-  if (pro) {
-    float* qt = reinterpret_cast<float*>(bqs + slots * KS * 512);
-    const uint32_t U1 = first_unit((blockIdx.x + 1) * wpg, sp);
-    const int ng = (int)((U1 - 1) / sp.upg - g_wg) + 1;  // at most slots
-    build_queries<D>(q, q_dtype, G, g_wg, ng, R, qscale, qt, bqs, qss);
+  bool has_lo = false;
+  float cs = kCs, ci = 1.0f / kCs;
+#pragma unroll 1
+  for (bool again = false;; again = true) {
+    bool lo_any = false;
+    float top = 0.0f;
+    for (int i = tid; i < nrow; i += nthr) {
+      float cv[4];
+      if (pair_n > 0) {
+        __builtin_memcpy(cv, C + 2 * (i % pair_n), 8);
+        __builtin_memcpy(cv + 2, C + 2 * (i / pair_n), 8);
+      } else {
+        __builtin_memcpy(cv, C + (size_t)i * 4, 16);
+      }
+      h4 hi, lo;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        hi[e] = (_Float16)(cv[e] * cs);
+        lo[e] = (_Float16)fmaf(cv[e], cs, -(float)hi[e]);
+        lo_any |= (float)lo[e] != 0.0f;
+        top = fmaxf(top, fabsf(cv[e]));
+      }
+      reinterpret_cast<h4*>(smem)[i] = hi;
+      reinterpret_cast<h4*>(smem)[nrow + i] = lo;
+    }
+    top = wave_max_dpp(top);
+    lo_any = __any(lo_any);
+    if (lane == 0) {
+      cmax[wave] = top;
+      clo[wave] = lo_any;
+    }
+    if (pro && !again) {
+      float* qt = reinterpret_cast<float*>(bqs + slots * KS * 512);
+      const uint32_t U1 = first_unit((blockIdx.x + 1) * wpg, sp);
+      const int ng = (int)((U1 - 1) / sp.upg - g_wg) + 1;  // at most slots
+      build_queries<D>(q, q_dtype, G, g_wg, ng, R, qscale, qt, bqs, qss);
+    }
+    __syncthreads();
+    has_lo = __any(lane < wpg && clo[lane & (kWavesWhole - 1)] != 0);
+    top = wave_max_dpp(lane < wpg ? cmax[lane & (kWavesWhole - 1)] : 0.0f);
+    if (again || top == 0.0f || (top >= 0x1p-6f && top < 15.9f)) break;
+    int e2 = 0;
+    frexpf(top, &e2);
+    e2 = top < INFINITY ? min(max(14 - e2, -100), 100) : 0;
+    cs = ldexpf(1.0f, e2);
+    ci = ldexpf(1.0f, -e2);
+    __syncthreads();  // (the flags are written again)
   }
-  const bool has_lo = __syncthreads_or(lo_any) != 0;
   h8 bqv[KS];
   f4 acc[VM];
   float m_run = -INFINITY, l_run = 0.0f, qsg = 1.0f;
@@ -461,7 +491,7 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
     for (int mu = 0; mu < VM; ++mu) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float a = fmaf(__shfl_xor(acc[mu][e], 32, 64), 0x1p-11f, acc[mu][e]);
+        const float a = fmaf(__shfl_xor(acc[mu][e], 32, 64), 0x1p-11f, acc[mu][e]) * ci;
         // row 4 g16 + e is head 4 g16 + e; column c is dim
         // 4 ((c / 4) (D / 16) + mu) + c % 4
         const int h = 4 * g16 + e;
@@ -610,7 +640,7 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
         if (cur_group >= 0) flush(past(cur_group));
         cur_group = grp;
         const _Float16* bqg = pro ? bqs + (grp - g_wg) * KS * 512 : bq + grp * KS * 512;
-        qsg = pro ? qss[grp - g_wg] : qsc[grp];
+        qsg = (pro ? qss[grp - g_wg] : qsc[grp]) * ci;
 #pragma unroll
         for (int kap = 0; kap < KS; ++kap) {
           bqv[kap] = *reinterpret_cast<const h8*>(bqg + kap * 512 + lane * 8);

@@ -794,6 +794,37 @@ def test_attention_row_codes(d, k, N, G, n_g, T, T_stride, fp16_cb, device):
     assert rel.max() <= 2.0 ** -20 * reach * 1.4427 + 2.0 ** -18, rel.max()
 
 
+@pytest.mark.parametrize("d,k,N,G,n_g,T", [(64, 4, 16, 8, 3, 333), (64, 8, 64, 4, 40, 700),
+                                           (64, 16, 256, 1, 2, 65), (64, 2, 16, 8, 3, 257),
+                                           (128, 8, 16, 4, 2, 300), (64, 4, 256, 3, 2100, 40)])
+@pytest.mark.parametrize("top", [1e-4, 2.0 ** -7, 0.9, 15.85, 16.0, 300.0, 1e6])
+def test_attention_codebook_scales(d, k, N, G, n_g, T, top, device):
+    """The matrix-core attention over float32 codebooks whose largest entry is
+    `top`, on both sides of the range that is staged at the fixed scale, far
+    below it and beyond binary16's: entries carry 22 bits whatever their
+    scale.  Bound: as in test_attention_row_codes, with the reach of the
+    decoded keys."""
+    R = oracle_rotation(d)
+    rng = np.random.default_rng(N + T)
+    C = rng.standard_normal((N, k))
+    C = (C * (top / np.abs(C).max())).astype(np.float32)
+    Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
+    q, kp, hk, vp, hv = _random_attention_inputs(rng, n_g, T, d, k, N, G, kscale=min(1.0 / top, 3e4))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(device)
+    _say(f"[edge] attention codebook up to {top:g} d={d} k={k} N={N} G={G} n_g={n_g} T={T}")
+    o = fq.attn_decode(dev(q), dev(kp), dev(occ.fp16_bits(hk).view(np.int16)), dev(vp),
+                       dev(occ.fp16_bits(hv).view(np.int16)), T, k, N, Rd, Cd).cpu().numpy()
+    some = sorted({0, n_g // 2, n_g - 1})
+    ref = gh.oracle_group_attention(q[some].astype(np.float64), kp[some], occ.fp16_bits(hk)[some],
+                                    vp[some], occ.fp16_bits(hv)[some], R, C, N, T)
+    rel = np.linalg.norm(o[some] - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    y = np.linalg.norm(C[occ.unpack(kp[some].reshape(-1, kp.shape[-1]), d // k, N)].reshape(-1, d), axis=1)
+    reach = (np.linalg.norm(q[some], axis=-1).max() / np.sqrt(d)
+             * (y * hk[some].reshape(-1).astype(np.float64)).max())
+    _say(f"  max rel l2 {rel.max():.2e}")
+    assert rel.max() <= 2.0 ** -20 * reach * 1.4427 + 2.0 ** -18, rel.max()
+
+
 def test_attention_zero_query_is_mean_value(device):
     """q = 0: every score is 0, the output is the mean decoded value."""
     d, k, N, G, T = 128, 4, 4096, 4, 300
