@@ -64,6 +64,7 @@ constexpr int kMaxWgs = 512;     // split plans: two workgroups per compute unit
 constexpr int kStep = 32;        // tokens per unit
 constexpr int kHeadBlocks = 2048;  // merge: a block per head up to so many heads
 constexpr float kCs = 4096.0f;   // scale of the codebook's binary16 rows
+constexpr float kVs = 16384.0f;  // scale of the weights while all value norms are below 2
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
@@ -478,6 +479,13 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
   h8 bqv[KS];
   f4 acc[VM];
   float m_run = -INFINITY, l_run = 0.0f, qsg = 1.0f;
+  // Scale of the weights p nu_V: a binary16 part holds 11 bits only above
+  // 2^-14, and value norms go down to 2^-24.  wsc starts at 2^14 in every group
+  // and drops to 1 at the first norm of 2 or more (wmask: the exponent bit that
+  // says so, in both halves of a word; 0 from then on); avs undoes it.
+  _Float16 wsc = (_Float16)kVs;
+  uint32_t wmask = 0x40004000u;
+  float avs = ci / kVs;
   int64_t cur_group = -1;
 
   auto flush = [&](auto* r) {
@@ -491,7 +499,7 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
     for (int mu = 0; mu < VM; ++mu) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float a = fmaf(__shfl_xor(acc[mu][e], 32, 64), 0x1p-11f, acc[mu][e]) * ci;
+        const float a = fmaf(__shfl_xor(acc[mu][e], 32, 64), 0x1p-11f, acc[mu][e]) * avs;
         // row 4 g16 + e is head 4 g16 + e; column c is dim
         // 4 ((c / 4) (D / 16) + mu) + c % 4
         const int h = 4 * g16 + e;
@@ -547,7 +555,8 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
       for (int e = 0; e < 4; ++e) t4[e] = (ts + e < T) ? t4[e] : -INFINITY;
     }
     const float tmx = fmaxf(fmaxf(t4[0], t4[1]), fmaxf(t4[2], t4[3]));
-    if (__any(tmx > 0.0f)) {  // a token beats the running maximum
+    const uint32_t big = (b.nv[0] | b.nv[1]) & wmask;
+    if (__any(tmx > 0.0f || big != 0)) {  // a token beats the running maximum, or a value norm its range
       // the maximum first, then every score against it in one fma (a score
       // of 100 rounded by itself would move its weight by 4e-6)
       const bool first = m_run == -INFINITY;  // nothing accumulated yet for this group
@@ -574,9 +583,16 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
       }
       const float alpha = __builtin_amdgcn_exp2f(-delta * qsg);
       l_run *= alpha;
+      float beta = 1.0f;
+      if (__any(big != 0)) {
+        beta = 1.0f / kVs;
+        wsc = (_Float16)1.0f;
+        wmask = 0;
+        avs = ci;
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {  // accumulator row 4 g16 + e belongs to head (4 g16 + e) & 7
-        const float ar = __shfl(alpha, (4 * g16 + e) & 7, 64);
+        const float ar = __shfl(alpha, (4 * g16 + e) & 7, 64) * beta;
 #pragma unroll
         for (int mu = 0; mu < VM; ++mu) acc[mu][e] *= ar;
       }
@@ -594,7 +610,7 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
     u4v au;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const h2 nv2 = __builtin_bit_cast(h2, b.nv[i]);
+      const h2 nv2 = __builtin_bit_cast(h2, b.nv[i]) * h2{wsc, wsc};  // (exact: norms below 2, or times 1)
       const float w0 = p[2 * i] * (float)nv2[0], w1 = p[2 * i + 1] * (float)nv2[1];
       uint32_t uh = __builtin_bit_cast(uint32_t, h2{(_Float16)w0, (_Float16)w1});
       asm("" : "+v"(uh));  // the rest is taken from these bits (not from a conversion fused anew)
@@ -649,6 +665,9 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
         for (int mu = 0; mu < VM; ++mu) acc[mu] = f4{0, 0, 0, 0};
         m_run = -INFINITY;
         l_run = 0.0f;
+        wsc = (_Float16)kVs;
+        wmask = 0x40004000u;
+        avs = ci / kVs;
       }
       int64_t ngrp = grp;
       int nstep = step + 1;

@@ -825,6 +825,38 @@ def test_attention_codebook_scales(d, k, N, G, n_g, T, top, device):
     assert rel.max() <= 2.0 ** -20 * reach * 1.4427 + 2.0 ** -18, rel.max()
 
 
+@pytest.mark.parametrize("d,k,N,G,n_g,T", [(64, 4, 16, 8, 3, 333), (64, 16, 256, 1, 2, 900),
+                                           (64, 2, 64, 8, 40, 257), (128, 8, 16, 4, 300, 300),
+                                           (64, 4, 256, 3, 700, 65)])
+@pytest.mark.parametrize("law", ["3e-7", "1e-5", "1e-3", "1.9", "rising", "falling"])
+def test_attention_small_value_norms(d, k, N, G, n_g, T, law, device):
+    """The matrix-core attention over values whose norms are far below 1 (down
+    to binary16's subnormals), just below 2, and in runs of small norms with
+    large ones behind or before them: the weights p nu_V carry 22 bits
+    whatever the norms.  Bound: as in test_attention_row_codes."""
+    R, C = oracle_rotation(d), quick_codebook(d, k, N)
+    rng = np.random.default_rng(N + T)
+    q, kp, hk, vp, _ = _random_attention_inputs(rng, n_g, T, d, k, N, G, kscale=2.0)
+    u = rng.uniform(0.5, 1.0, (n_g, T))
+    if law in ("rising", "falling"):  # the large norms begin (end) in the middle of a group
+        big = np.arange(T) >= T // 2 if law == "rising" else np.arange(T) < T // 2
+        hv = (u * np.where(big, 30.0, 1e-5)).astype(np.float16)
+    else:
+        hv = (u * float(law)).astype(np.float16)
+    Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(device)
+    _say(f"[edge] attention value norms {law} d={d} k={k} N={N} G={G} n_g={n_g} T={T}")
+    o = fq.attn_decode(dev(q), dev(kp), dev(occ.fp16_bits(hk).view(np.int16)), dev(vp),
+                       dev(occ.fp16_bits(hv).view(np.int16)), T, k, N, Rd, Cd).cpu().numpy()
+    some = sorted({0, n_g // 2, n_g - 1})
+    ref = gh.oracle_group_attention(q[some].astype(np.float64), kp[some], occ.fp16_bits(hk)[some],
+                                    vp[some], occ.fp16_bits(hv)[some], R, C, N, T)
+    rel = np.linalg.norm(o[some] - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    reach = np.linalg.norm(q[some], axis=-1).max() * hk.astype(np.float64).max() / np.sqrt(d)
+    _say(f"  max rel l2 {rel.max():.2e}")
+    assert rel.max() <= 2.0 ** -20 * reach * 1.4427 + 2.0 ** -18, rel.max()
+
+
 def test_attention_zero_query_is_mean_value(device):
     """q = 0: every score is 0, the output is the mean decoded value."""
     d, k, N, G, T = 128, 4, 4096, 4, 300
