@@ -556,7 +556,9 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
     }
     const float tmx = fmaxf(fmaxf(t4[0], t4[1]), fmaxf(t4[2], t4[3]));
     const uint32_t big = (b.nv[0] | b.nv[1]) & wmask;
-    if (__any(tmx > 0.0f || big != 0)) {  // a token beats the running maximum, or a value norm its range
+    // a token beats the running maximum or a value norm its range, or (not a
+    // number) no finite score has come yet and an infinite key norm scores -inf
+    if (__any(!(tmx <= 0.0f) || big != 0)) {
       // the maximum first, then every score against it in one fma (a score
       // of 100 rounded by itself would move its weight by 4e-6)
       const bool first = m_run == -INFINITY;  // nothing accumulated yet for this group
@@ -578,8 +580,8 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const h2 nk2 = __builtin_bit_cast(h2, b.nk[e >> 1]);
-        const float t = fmaf(f4s[e], (float)nk2[e & 1], -m_run);
-        t4[e] = (full || ts + e < T) ? t : -INFINITY;
+        const float nk = (float)nk2[e & 1], t = fmaf(f4s[e], nk, -m_run);
+        t4[e] = (full || ts + e < T) && f4s[e] * nk != -INFINITY ? t : -INFINITY;  // (weight 0)
       }
       const float alpha = __builtin_amdgcn_exp2f(-delta * qsg);
       l_run *= alpha;

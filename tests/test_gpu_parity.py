@@ -857,6 +857,39 @@ def test_attention_small_value_norms(d, k, N, G, n_g, T, law, device):
     assert rel.max() <= 2.0 ** -20 * reach * 1.4427 + 2.0 ** -18, rel.max()
 
 
+@pytest.mark.parametrize("d,k,N,T", [(64, 4, 16, 333), (64, 16, 256, 65), (128, 8, 16, 1000), (64, 4, 256, 40)])
+def test_attention_infinite_key_norms(d, k, N, T, device):
+    """Keys with an infinite norm header that score minus infinity have weight
+    0 wherever they stand: as a group's whole first units, in between, and as
+    all of its tokens (output 0), as in the general kernels."""
+    R, C = oracle_rotation(d), quick_codebook(d, k, N)
+    R64, C64 = R.astype(np.float64), C.astype(np.float64)
+    rng = np.random.default_rng(T)
+    q, kp, hk, vp, hv = _random_attention_inputs(rng, 4, T, d, k, N, 1, kscale=2.0)
+    idx = occ.unpack(kp.reshape(4 * T, -1), d // k, N).reshape(4, T, d // k)
+    for g in range(4):
+        unit = occ.decode(idx[g], np.ones(T, np.float16), R64, C64) @ q[g, 0].astype(np.float64)
+        low = idx[g, int(unit.argmin())]  # a key of negative score
+        assert unit.min() < -0.1
+        tokens = {0: np.arange(min(T - 1, 40)), 1: np.flatnonzero(rng.random(T) < 0.3),
+                  2: np.arange(T), 3: np.arange(T - 3, T)}[g]
+        idx[g, tokens] = low
+        hk[g, tokens] = np.inf
+    kp = occ.pack(idx.reshape(4 * T, -1), N).reshape(4, T, -1)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(device)
+    _say(f"[edge] attention infinite key norms d={d} k={k} N={N} T={T}")
+    o = fq.attn_decode(dev(q), dev(kp), dev(occ.fp16_bits(hk).view(np.int16)), dev(vp),
+                       dev(occ.fp16_bits(hv).view(np.int16)), T, k, N, dev(R.copy()), dev(C.copy())).cpu().numpy()
+    assert np.all(o[2] == 0), o[2]
+    for g in (0, 1, 3):
+        keep = np.isfinite(hk[g])
+        ref = gh.oracle_group_attention(q[g:g + 1].astype(np.float64), kp[g:g + 1, keep],
+                                        occ.fp16_bits(hk[g])[None, keep], vp[g:g + 1, keep],
+                                        occ.fp16_bits(hv[g])[None, keep], R, C, N, int(keep.sum()))
+        rel = np.linalg.norm(o[g] - ref[0]) / np.linalg.norm(ref)
+        assert rel <= 1e-5, (g, rel)
+
+
 def test_attention_zero_query_is_mean_value(device):
     """q = 0: every score is 0, the output is the mean decoded value."""
     d, k, N, G, T = 128, 4, 4096, 4, 300
