@@ -66,15 +66,34 @@ static AttnPlan make_plan(int64_t n_groups, int G, int64_t T, const Shape& s) {
   return p;
 }
 
+// Many short groups with one or two heads: the matrix-core kernel needs its
+// query preparation as a third launch there and leaves a record of 8 heads for
+// every group, while the general kernels have one workgroup per group and
+// little to do in it, unless that stages a codebook of some KB for so few
+// tokens (above kCbLds floats it is read from global memory).  us, general /
+// matrix-core kernel:
+//   (64, 8, 16)    G = 1, 33 tokens: 1000 groups 28.0 / 19.3, 4000 32.2 / 45.5, 10000 67.7 / 84.0
+//                  G = 2: 2000 of 64 28.5 / 28.8, 4000 of 64 43.0 / 48.8, 10000 of 33 98.0 / 90.3
+//   (64, 8, 1024)  G = 1, 33 tokens: 2000 groups 35.9 / 29.2
+//   (64, 8, 4096)  G = 1, 64 tokens: 1000 groups 28.3 / 23.7, 2000 28.1 / 35.6
+//   (128, 8, 16)   G = 1, 64 tokens: 300 groups 28.8 / 23.0, 1000 28.5 / 30.9, 2000 39.2 / 54.5
+static bool short_groups(int64_t n_groups, int G, int64_t T, const Shape& s) {
+  const int nk = s.N * s.k;
+  return G <= 2 && T <= (G == 1 && nk <= 128 ? 128 : 64) && n_groups >= (s.d == 64 ? 1536 : 512) &&
+         (G == 1 || n_groups < (s.d == 64 ? 4608 : 1152)) &&
+         (nk <= (G == 1 ? 2048 : 512) || nk > 16384);
+}
+
 // Whether a call takes the matrix-core kernel of attn_k4.hip.  Codes that it
 // reads with run-time index widths may need more workspace there than in the
 // general kernels (8 heads' records whatever G): they stay here where that
 // would no longer fit the static scratch.
 static bool use_k4(int64_t n_groups, int G, int64_t T, const Shape& s) {
   if (!attn_k4_applies(G, s) || !attn_k4_fits(n_groups, T)) return false;
+  if (s.k == 2 || (s.k == 4 && (s.w == 8 || s.w == 12)) || (s.k == 8 && s.w == 6 && G == 8)) return true;
+  if (short_groups(n_groups, G, T, s)) return false;
   const size_t need = attn_k4_workspace_bytes(n_groups, T, s);
-  return need <= FIBQ_ATTN_SCRATCH_BYTES || need <= make_plan(n_groups, G, T, s).total ||
-         s.k == 2 || (s.k == 4 && (s.w == 8 || s.w == 12)) || (s.k == 8 && s.w == 6 && G == 8);
+  return need <= FIBQ_ATTN_SCRATCH_BYTES || need <= make_plan(n_groups, G, T, s).total;
 }
 
 size_t attn_workspace_bytes(int64_t n_groups, int G, int64_t T, Shape s) {

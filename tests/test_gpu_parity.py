@@ -890,6 +890,30 @@ def test_attention_infinite_key_norms(d, k, N, T, device):
         assert rel <= 1e-5, (g, rel)
 
 
+@pytest.mark.parametrize("d,k,N,G,n_g,T", [
+    (64, 8, 16, 1, 1535, 64), (64, 8, 16, 1, 1536, 64), (64, 8, 16, 1, 1536, 128), (64, 8, 16, 1, 1536, 129),
+    (64, 8, 256, 1, 1536, 65), (64, 4, 1024, 1, 1536, 33), (64, 8, 4096, 2, 1536, 7), (64, 8, 64, 2, 4608, 33),
+    (64, 16, 256, 2, 1700, 64), (128, 8, 16, 1, 511, 64), (128, 8, 16, 1, 512, 64), (128, 16, 64, 2, 600, 8),
+    (128, 8, 16, 2, 1152, 33)])
+def test_attention_short_groups(d, k, N, G, n_g, T, device):
+    """Many short groups with one or two heads, on both sides of the sizes at
+    which they go to the general kernels.  Bound: as in
+    test_attention_row_codes."""
+    R, C = oracle_rotation(d), quick_codebook(d, k, N)
+    rng = np.random.default_rng(n_g + T)
+    q, kp, hk, vp, hv = _random_attention_inputs(rng, n_g, T, d, k, N, G, kscale=2.0)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(device)
+    _say(f"[edge] attention short groups d={d} k={k} N={N} G={G} n_g={n_g} T={T}")
+    o = fq.attn_decode(dev(q), dev(kp), dev(occ.fp16_bits(hk).view(np.int16)), dev(vp),
+                       dev(occ.fp16_bits(hv).view(np.int16)), T, k, N, dev(R.copy()), dev(C.copy())).cpu().numpy()
+    some = [0, 1, n_g // 2, n_g - 2, n_g - 1]
+    ref = gh.oracle_group_attention(q[some].astype(np.float64), kp[some], occ.fp16_bits(hk)[some],
+                                    vp[some], occ.fp16_bits(hv)[some], R, C, N, T)
+    rel = np.linalg.norm(o[some] - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    reach = np.linalg.norm(q[some], axis=-1).max() * hk.astype(np.float64).max() / np.sqrt(d)
+    assert rel.max() <= 2.0 ** -20 * reach * 1.4427 + 2.0 ** -18, rel.max()
+
+
 def test_attention_zero_query_is_mean_value(device):
     """q = 0: every score is 0, the output is the mean decoded value."""
     d, k, N, G, T = 128, 4, 4096, 4, 300
