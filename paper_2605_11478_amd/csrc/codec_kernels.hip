@@ -862,11 +862,11 @@ static int num_cus() {
   return n;
 }
 
-// the exhaustive general encoder's block dimensions: k = d = 64, and k = 1, 2
-// for N > 2048; the others are encode_gen.hip's (147456 rows of k = 8,
-// N = 1024: 1124 us here, 91 there)
-template <int K>
-constexpr bool scans_all() { return K < 4 || K == 64; }
+// the exhaustive general encoder's block dimensions: k = d = 64, k = 1, 2 for
+// N > 2048, and the codes of scan_rows; the others are encode_gen.hip's (147456
+// rows of k = 8, N = 1024: 1124 us here, 91 there)
+template <int D, int K>
+constexpr bool scans_all() { return K < 4 || K == 64 || (D == 64 && K == 4); }
 
 template <typename IN, int D, int K, bool CG>
 static int launch_encode_cg(const void* x, int64_t n_vec, int64_t stride, const Shape& s,
@@ -877,7 +877,7 @@ static int launch_encode_cg(const void* x, int64_t n_vec, int64_t stride, const 
                      sizeof(float) * (size_t)((CG ? 0 : s.N * K) + s.N + 4) +
                      (size_t)kEncThreads * s.P;
   const void* kern = reinterpret_cast<const void*>(&encode_shells_kernel<IN, D, K, CG>);
-  if constexpr (scans_all<K>())
+  if constexpr (scans_all<D, K>())
     if (!sm) kern = reinterpret_cast<const void*>(&encode_kernel<IN, D, K, CG>);
   hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return (int)e;
@@ -888,7 +888,7 @@ static int launch_encode_cg(const void* x, int64_t n_vec, int64_t stride, const 
     hipLaunchKernelGGL((encode_shells_kernel<IN, D, K, CG>), dim3(grid), dim3(kEncThreads), lds,
                        st, static_cast<const IN*>(x), n_vec, stride, R, C, s.N, s.w, s.P, payload,
                        norms, L, *sm);
-  if constexpr (scans_all<K>())
+  if constexpr (scans_all<D, K>())
     if (!sm)
       hipLaunchKernelGGL((encode_kernel<IN, D, K, CG>), dim3(grid), dim3(kEncThreads), lds, st,
                          static_cast<const IN*>(x), n_vec, stride, R, C, s.N, s.w, s.P, payload,
@@ -976,6 +976,23 @@ static int64_t few_rows(const Shape& s) {
   return s.N == 256 ? 65536 : s.N == 64 ? 40960 : 20480;
 }
 
+// From so many rows (on 256 compute units) the general encoder's one thread per
+// vector is faster than encode_gen.hip for codes that it scans in few steps
+// (k = 4, N <= 16 at d = 64, where encode_gen pads to 64 codewords and rescores
+// 16) and for those whose every block is a near tie in float32, which it
+// rescores 64 at a time (k = 1, N >= 1024).  us, general / encode_gen, d = 64:
+//   (4, 4) bf16     65536 rows 31.4 / 28.6, 98304 39.0 / 43.0, 163840 65.6 / 68.0, 2000000 556 / 813
+//   (4, 8) fp32     98304 rows 45.4 / 43.4, 131072 46.2 / 52.7, 262144 87.3 / 105.7
+//   (4, 16) fp32    131072 rows 52.2 / 52.6, 196608 86.9 / 82.2, 262144 98.8 / 106.2, 700000 246 / 278
+//   (4, 32) fp32    262144 rows 123 / 106
+//   (1, 1024) bf16  32768 rows 5647 / 2294, 131072 5956 / 8274 (d = 128: 24218 / 19215)
+//   (1, 512) bf16   131072 rows 3015 / 1805
+static int64_t scan_rows(const Shape& s) {
+  if (s.d == 64 && s.k == 4 && s.N <= 16) return s.N <= 8 ? 90112 : 229376;
+  if (s.d == 64 && s.k == 1 && s.N >= 1024) return 90112;
+  return INT64_MAX;
+}
+
 int launch_encode(const void* x, int dtype, int64_t n_vec, int64_t stride, Shape s,
                   const float* R, const float* C, uint8_t* payload, uint16_t* norms,
                   void* stream) {
@@ -987,7 +1004,7 @@ int launch_encode(const void* x, int dtype, int64_t n_vec, int64_t stride, Shape
     if (encode_mf4_applies(dtype, s, x, stride, R, payload, norms))
       return launch_encode_mf4(x, dtype, n_vec, stride, s, R, C, payload, norms, stream, n_cu);
   }
-  if (encode_gen_applies(s))
+  if (encode_gen_applies(s) && n_vec / n_cu < scan_rows(s) / 256)
     return launch_encode_gen(x, dtype, n_vec, stride, s, R, C, payload, norms, stream, n_cu);
   return dispatch_dtype(x, dtype, n_vec, stride, s, R, C, payload, norms, 1, nullptr, st);
 }

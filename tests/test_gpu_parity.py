@@ -574,6 +574,39 @@ def test_encode_tile_kernels_match_few_rows(k, N, dtype, n, device):
     gh.check_encode(gh.host_f64(x[some]), R, C, N, p[some.to(device)], nrm[some.to(device)])
 
 
+@pytest.mark.parametrize("k,N,dtype,n,pad", [
+    (4, 2, torch.bfloat16, 90112, 0), (4, 8, torch.float16, 90111, 1), (4, 8, torch.float32, 90113, 3),
+    (4, 16, torch.float32, 229377, 0), (4, 16, torch.bfloat16, 229376, 1), (1, 1024, torch.bfloat16, 90115, 0)])
+def test_encode_scan_rows(k, N, dtype, n, pad, device):
+    """Codes that go to the general one-thread-per-vector encoder from a number
+    of rows on: the bytes of calls over fewer rows (the matrix-core encoder
+    or its scan), and a sample of rows is the oracle's; zero rows, an infinite
+    one, duplicated codewords, strided and unaligned rows, a ragged end."""
+    d = 64
+    R = oracle_rotation(d)
+    rng = np.random.default_rng(N + n)
+    C = np.sort(rng.standard_normal((N, k)), axis=0) * rng.uniform(0.4, 1.0, (N, 1)) * np.sqrt(1.0 / d)
+    C = C.astype(np.float32)
+    if N > 2:
+        C[N - 1] = C[N // 2]
+    Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
+    g = torch.Generator().manual_seed(n)
+    x = torch.randn(n, d + pad, generator=g) * torch.exp(torch.randn(n, 1, generator=g))
+    x[5] = x[n - 1] = 0
+    x[300, pad + 7] = float("inf")
+    x = x.to(dtype)
+    xd = x.to(device)[:, pad:]
+    _say(f"[edge] encode scan rows k={k} N={N} {dtype} n={n} pad={pad}")
+    p, nrm = fq.encode(xd, k, N, Rd, Cd)
+    few = [fq.encode(c, k, N, Rd, Cd) for c in xd.split(30000)]
+    torch.cuda.synchronize()
+    assert torch.equal(nrm, torch.cat([f[1] for f in few]))
+    assert torch.equal(p, torch.cat([f[0] for f in few]))
+    some = torch.cat([torch.arange(0, 40), torch.arange(65520, 65560), torch.arange(n - 40, n)])
+    gh.check_encode(gh.host_f64(x[some, pad:]), R, C, N, p[some.to(device)], nrm[some.to(device)])
+    assert not p[300].any() and int(gh.bits_u16(nrm)[300]) == 0x7C00
+
+
 @pytest.mark.parametrize("k,N", [(8, 16), (4, 256)])
 def test_decode_out_of_range_ids_give_nan(k, N, device):
     """Both decoders (the LDS table for small codebooks, the Pi^T product
