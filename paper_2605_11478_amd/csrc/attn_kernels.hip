@@ -428,9 +428,6 @@ int launch_attn(const void* q, int q_dtype, const uint8_t* kp, const uint16_t* k
       (s.k > 4 || ((reinterpret_cast<uintptr_t>(kp) | reinterpret_cast<uintptr_t>(vp)) & 3u) == 0))
     return launch_attn_k4(q, q_dtype, kp, kn, vp, vn, n_groups, G, T, T_stride, s, R, C, scale,
                           out, ws, st);
-  if (attn_w4_applies(G, s) && attn_k4_fits(n_groups, T) && norms2)
-    return launch_attn_w4(q, q_dtype, kp, kn, vp, vn, n_groups, T, T_stride, R, C, scale, out, ws,
-                          st);
 #define FIBQ_ATTN_CASE(DD, KK)                                                                 \
   if (s.d == DD && s.k == KK)                                                               \
     return launch_attn_t<DD, KK>(q, q_dtype, kp, kn, vp, vn, n_groups, G, T, T_stride, s, R, C, \

@@ -876,6 +876,7 @@ static int launch_encode_cg(const void* x, int64_t n_vec, int64_t stride, const 
   const size_t lds = sizeof(PT) * D * D + (sm ? 8 * kMaxShells : 0) +
                      sizeof(float) * (size_t)((CG ? 0 : s.N * K) + s.N + 4) +
                      (size_t)kEncThreads * s.P;
+  if (!scans_all<D, K>() && !sm) return (int)hipErrorInvalidValue;
   const void* kern = reinterpret_cast<const void*>(&encode_shells_kernel<IN, D, K, CG>);
   if constexpr (scans_all<D, K>())
     if (!sm) kern = reinterpret_cast<const void*>(&encode_kernel<IN, D, K, CG>);
