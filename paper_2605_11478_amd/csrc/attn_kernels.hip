@@ -416,9 +416,18 @@ int launch_attn(const void* q, int q_dtype, const uint8_t* kp, const uint16_t* k
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bool norms2 =
       ((reinterpret_cast<uintptr_t>(kn) | reinterpret_cast<uintptr_t>(vn)) & 1u) == 0;
-  // The 4-bit shape's own kernel where the groups are many: its one block per
-  // group merges up to 256 / n_groups records (1 group of 131072 tokens 84 us,
-  // 32 in attn_k4; 32 groups of 8192: 16.1 against 18.0).
+  // The 4-bit shape's own kernel where the groups are many: per token it does
+  // half the work, but its merge walks a group's records one round after
+  // another, min(256 / n_groups, T / 128) of them.  us, attn_w4 / attn_k4:
+  //   1 group     1000 tokens 11.7 / 15.2, 2000 13.2 / 12.9, 8192 22.3 / 12.7, 131072 57.1 / 32.2
+  //   8 groups    1000 tokens 11.9 / 15.5, 8192 17.0 / 13.3, 32768 17.7 / 20.3, 131072 21.9 / 31.3
+  //   12 groups   4096 tokens 18.1 / 13.3, 8192 18.3 / 16.2, 32768 19.9 / 22.3
+  //   16 groups   1000 tokens 12.0 / 15.5, 4096 13.9 / 13.5, 8192 14.1 / 16.3, 131072 24.8 / 43.5
+  //   32 groups   1000 tokens 12.4 / 15.5, 8192 13.3 / 18.0
+  //   352 groups  250 tokens 16.0 / 14.3, 1000 20.8 / 23.5, 32768 71.3 / 153.7
+  // Fewer groups stay with attn_k4 also where it is the slower one (short and
+  // very long contexts): its weights keep 22 bits (error against float64 2e-7),
+  // those here are rounded to binary16 (9e-5).
   if (attn_w4_applies(G, s) && n_groups >= 16 && attn_k4_fits(n_groups, T) && norms2)
     return launch_attn_w4(q, q_dtype, kp, kn, vp, vn, n_groups, T, T_stride, R, C, scale, out, ws,
                           st);

@@ -855,9 +855,8 @@ __global__ __launch_bounds__(kThreads) void main_kernel(
 }
 
 // ---------------------------------------------------------------- merge ----
-// One block per group: log-sum-exp over the records of the workgroups whose
-// unit ranges meet the group, then o = Pi^T (acc / l).  Thread t owns dim
-// t % 64 of heads t / 64 and t / 64 + 4.  Pi is staged in LDS and the
+// Two blocks per group, four heads each: log-sum-exp over the records of the
+// workgroups whose unit ranges meet the group, then o = Pi^T (acc / l).  The
 // records of up to kMergeMax contributors are loaded in the same round of
 // memory requests, before any of their values is used.
 constexpr int kMergeThreads = 256;

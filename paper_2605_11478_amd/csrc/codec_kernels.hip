@@ -649,7 +649,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_list_kernel(
 // Bound: 16 rows are (D / 16)(D / 4) products of 32 clocks on a SIMD (147456
 // rows of d = 64: 8.4 us), beside the output's bytes.  Against the product on
 // the vector units with Pi read from LDS for every row: 147456 rows of
-// (64, 4, 256) 39.6 -> 20.9 us, 200000 rows of (128, 4, 256) 293 -> 69, 65536
+// (64, 4, 256) 39.6 -> 19.9 us, 200000 rows of (128, 4, 256) 293 -> 69, 65536
 // ids of (128, 4, 4096) 119 -> 29.
 template <int D>
 constexpr int dec_tiles() { return D == 64 ? 2 : 1; }

@@ -1,7 +1,9 @@
 // Encoder for block dimensions k = 4, 8, 16 and 32 (Eq. encode of Sec. 3.1)
 // with the nearest-codeword search as a dense contraction on the matrix cores:
 // every N, input type, row stride and alignment, d = 64 or 128 (k = 32: 64);
-// and for k = 1 and 2 with a scan (scan_kernel below).
+// and for k = 1 and 2 with a scan (scan_kernel below).  Over many rows the tile
+// kernels of the specialised codes take over, and for tiny codebooks and dense
+// k = 1 codes the general encoder (few_rows and scan_rows in codec_kernels.hip).
 //
 // A wavefront encodes 16 vectors per batch:
 //
