@@ -41,6 +41,61 @@ def _say(*a):
     print(*a, flush=True)
 
 
+# Rows above which 16-bit rows of d = 64 go to the tile encoders (on 256 compute
+# units; calls of fewer rows go to the general matrix-core encoder)
+TILE_ROWS = {(8, 16): 16384, (8, 64): 327680, (4, 256): 57344, (4, 64): 28672, (4, 16): 8192,
+             (2, 256): 65536, (2, 64): 40960, (2, 16): 20480}
+
+
+def _encode_both(xd, k, N, Rd, Cd):
+    """Encodes the rows in a call over them alone and, for a code and type that
+    has a tile encoder, in one over so many copies of them (a ragged number of
+    rows, the same row stride) that it takes the tile encoder: the copies'
+    bytes have to be those of the first call, which are returned."""
+    p, nrm = fq.encode(xd, k, N, Rd, Cd)
+    if (k, N) not in TILE_ROWS or xd.shape[1] != 64 or xd.dtype == torch.float32 or \
+            (k == 8 and xd.dtype != torch.bfloat16):
+        return p, nrm
+    n, d = xd.shape
+    cus = torch.cuda.get_device_properties(xd.device).multi_processor_count
+    copies = TILE_ROWS[(k, N)] * cus // 256 // n + 2
+    rows = copies * n - 3
+    big = xd.new_empty(rows, xd.stride(0))[:, :d]
+    big.copy_(xd.repeat(copies, 1)[:rows])
+    pb, nb = fq.encode(big, k, N, Rd, Cd)
+    torch.cuda.synchronize()
+    bad = (pb != p.repeat(copies, 1)[:rows]).any(1)
+    assert not bad.any(), f"{int(bad.sum())} of {rows} rows differ, first {int(bad.nonzero()[0])}"
+    assert torch.equal(nb, nrm.repeat(copies)[:rows])
+    _say(f"  the same bytes in a call over {rows} rows")
+    return p, nrm
+
+
+def _midpoint_rows(rng, n, R, C, dtype):
+    """n rows of which 7 of 8 (k = 8), half (k = 4) or a quarter (k = 2) of the
+    blocks of y sit at the midpoint of a codeword and its nearest neighbour,
+    the others random and scaled so that |y| = 1, rounded to dtype; and the
+    number of their blocks that the oracle finds within 1e-3 of a tie."""
+    d, (N, k) = R.shape[0], C.shape
+    C64 = C.astype(np.float64)
+    D2 = ((C64[:, None, :] - C64[None, :, :]) ** 2).sum(-1)
+    np.fill_diagonal(D2, np.inf)
+    nbr = D2.argmin(1)
+    m = {8: 7, 4: d // 8, 2: d // 8}[k]
+    a = rng.integers(0, N, size=(n, m))
+    mid = 0.5 * (C64[a] + C64[nbr[a]])                     # [n, m, k]
+    rest = 1.0 - (mid ** 2).sum(axis=(1, 2))
+    assert np.all(rest > 0)
+    last = rng.standard_normal((n, d - m * k))
+    last *= (np.sqrt(rest) / np.linalg.norm(last, axis=1))[:, None]
+    y = np.concatenate([mid.reshape(n, m * k), last], axis=1)
+    nu = np.exp(rng.uniform(-3.0, 3.0, size=(n, 1)))
+    x = torch.from_numpy((nu * (y @ R.astype(np.float64))).astype(np.float32)).to(dtype)
+    _, _, D = occ.encode(gh.host_f64(x), R.astype(np.float64), C64, return_distances=True)
+    Dsort = np.sort(D, axis=-1)
+    return x, int(((Dsort[..., 1] - Dsort[..., 0]) <= 1e-3 * Dsort[..., 1]).sum())
+
+
 @pytest.mark.parametrize("name,k,N", CASES)
 def test_encode_decode_attention_parity(name, k, N, device):
     wl = W.WORKLOADS[name]
@@ -122,7 +177,7 @@ def test_encode_edge_cases(dtype, device):
     xd = x.to(device)[:, :d]
     assert xd.stride(0) == 2 * d
     _say(f"[edge] encode dtype={dtype}")
-    p, nrm = fq.encode(xd, k, N, Rd, Cd)
+    p, nrm = _encode_both(xd, k, N, Rd, Cd)
     torch.cuda.synchronize()
     gh.check_encode(gh.host_f64(xs), R, C, N, p, nrm)
     assert int(gh.bits_u16(nrm)[3]) == 0 and not p.cpu().numpy()[3].any()
@@ -159,7 +214,7 @@ def test_encode_bf16_k8_screen_path(N, fp16_cb, device):
     xd = x.to(device)[:, :d]
     assert xd.stride(0) == 2 * d
     _say(f"[edge] bf16 k=8 screen path N={N} fp16 codebook={fp16_cb}")
-    p, nrm = fq.encode(xd, k, N, Rd, Cd)
+    p, nrm = _encode_both(xd, k, N, Rd, Cd)
     torch.cuda.synchronize()
     ne, nt, _, _ = gh.check_encode(gh.host_f64(xs), R, C, N, p, nrm)
     _say(f"  {ne} exact indices, {nt} accepted near-ties")
@@ -185,7 +240,7 @@ def test_encode_bf16_k8_many_out_of_range_rows(N, device):
         x[r] = (1e30 if r % 2 else 1e-30) * torch.randn(d, generator=g)
     x = x.to(torch.bfloat16)
     _say(f"[edge] bf16 k=8 many out-of-range rows N={N}")
-    p, nrm = fq.encode(x.to(device), k, N, Rd, Cd)
+    p, nrm = _encode_both(x.to(device), k, N, Rd, Cd)
     torch.cuda.synchronize()
     ne, nt, _, _ = gh.check_encode(gh.host_f64(x), R, C, N, p, nrm)
     _say(f"  {ne} exact indices, {nt} accepted near-ties")
@@ -224,7 +279,7 @@ def test_encode_bf16_k8_near_midpoints(N, device):
     Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
     _say(f"[edge] bf16 k=8 near midpoints N={N}: {close} blocks within 1e-3 relative")
     assert close > 1000
-    p, nrm = fq.encode(xs.to(device), k, N, Rd, Cd)
+    p, nrm = _encode_both(xs.to(device), k, N, Rd, Cd)
     torch.cuda.synchronize()
     ne, nt, _, _ = gh.check_encode(gh.host_f64(xs), R, C, N, p, nrm)
     _say(f"  {ne} exact indices, {nt} accepted near-ties")
@@ -269,7 +324,7 @@ def test_encode_k4_k2_screen_path(k, N, dtype, fp16_cb, device):
     xd = x.to(device)[:, :d]
     assert xd.stride(0) == 2 * d
     _say(f"[edge] k={k} N={N} {dtype} screen path fp16 codebook={fp16_cb}")
-    p, nrm = fq.encode(xd, k, N, Rd, Cd)
+    p, nrm = _encode_both(xd, k, N, Rd, Cd)
     torch.cuda.synchronize()
     ne, nt, _, _ = gh.check_encode(gh.host_f64(xs), R, C, N, p, nrm)
     _say(f"  {ne} exact indices, {nt} accepted near-ties")
@@ -311,7 +366,7 @@ def test_encode_k4_k2_near_midpoints(k, N, dtype, device):
     Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
     _say(f"[edge] k={k} N={N} {dtype} near midpoints: {close} blocks within 1e-3 relative")
     assert close > 1000
-    p, nrm = fq.encode(xs.to(device), k, N, Rd, Cd)
+    p, nrm = _encode_both(xs.to(device), k, N, Rd, Cd)
     torch.cuda.synchronize()
     ne, nt, _, _ = gh.check_encode(gh.host_f64(xs), R, C, N, p, nrm)
     _say(f"  {ne} exact indices, {nt} accepted near-ties")
@@ -336,7 +391,7 @@ def test_encode_k4_k2_many_out_of_range_rows(k, N, device):
         x[r] = (1e30 if r % 2 else 1e-30) * torch.randn(d, generator=g)
     x = x.to(torch.bfloat16)
     _say(f"[edge] bf16 k={k} N={N} many out-of-range rows")
-    p, nrm = fq.encode(x.to(device), k, N, Rd, Cd)
+    p, nrm = _encode_both(x.to(device), k, N, Rd, Cd)
     torch.cuda.synchronize()
     ne, nt, _, _ = gh.check_encode(gh.host_f64(x), R, C, N, p, nrm)
     _say(f"  {ne} exact indices, {nt} accepted near-ties")
@@ -391,7 +446,7 @@ def test_encode_k2_n64_grid_edge_cases(dtype, device):
     xs = torch.from_numpy(x).to(dtype)
     Rd, Cd = torch.from_numpy(R.astype(np.float32)).to(device), torch.from_numpy(C.copy()).to(device)
     _say(f"[edge] k=2 N=64 {dtype} grid edge cases")
-    p, nrm = fq.encode(xs.to(device), k, N, Rd, Cd)
+    p, nrm = _encode_both(xs.to(device), k, N, Rd, Cd)
     torch.cuda.synchronize()
     ne, nt, _, _ = gh.check_encode(gh.host_f64(xs), R.astype(np.float32), C, N, p, nrm)
     _say(f"  {ne} exact indices, {nt} accepted near-ties")
@@ -433,7 +488,7 @@ def test_encode_large_codebook_path(d, dtype, N, variant, device):
     xd = x.to(device)[:, :d]
     assert xd.stride(0) == 2 * d
     _say(f"[edge] large codebook path d={d} dtype={dtype} N={N} variant={variant}")
-    p, nrm = fq.encode(xd, k, N, Rd, Cd)
+    p, nrm = _encode_both(xd, k, N, Rd, Cd)
     torch.cuda.synchronize()
     ne, nt, _, _ = gh.check_encode(gh.host_f64(xs), R, C, N, p, nrm)
     _say(f"  {ne} exact indices, {nt} accepted near-ties")
@@ -495,7 +550,10 @@ def test_decode_kernels(d, k, N, n, device):
     (64, 2, 16, torch.float32, 4095, "dup"), (64, 2, 2048, torch.bfloat16, 47, "wide"),
     (128, 1, 8, torch.bfloat16, 8193, "plain"), (128, 2, 64, torch.float16, 8200, "strided"),
     (64, 4, 256, torch.bfloat16, 16385, "plain"), (64, 8, 64, torch.bfloat16, 40000, "dup"),
-    (128, 8, 64, torch.float32, 16400, "plain"), (64, 2, 64, torch.bfloat16, 32, "dup")])
+    (128, 8, 64, torch.float32, 16400, "plain"), (64, 2, 64, torch.bfloat16, 32, "dup"),
+    # k = 4 codebooks that pass through LDS in chunks, with equal codewords in two of them
+    (64, 4, 16384, torch.bfloat16, 43, "dup"), (128, 4, 16384, torch.float32, 21, "dup"),
+    (128, 4, 16384, torch.float16, 35, "strided")])
 def test_encode_matrix_core_general(d, k, N, dtype, n, variant, device):
     """The matrix-core encoder for any N at k = 4 to 32: one and two tiles of
     codewords, codebooks that pass through LDS in chunks, ragged batches of 16
@@ -534,42 +592,55 @@ def test_encode_matrix_core_general(d, k, N, dtype, n, variant, device):
         assert not p2[3].any() and int(gh.bits_u16(n2)[3]) == 0x7C00
 
 
-@pytest.mark.parametrize("k,N,dtype,n", [
-    (8, 16, torch.bfloat16, 20001), (8, 64, torch.bfloat16, 330007),
-    (4, 256, torch.bfloat16, 60011), (4, 256, torch.float16, 60011),
-    (4, 64, torch.float16, 30011), (4, 16, torch.bfloat16, 10013),
-    (2, 256, torch.bfloat16, 70001), (2, 64, torch.float16, 50021), (2, 16, torch.bfloat16, 30011)])
-def test_encode_tile_kernels_match_few_rows(k, N, dtype, n, device):
+@pytest.mark.parametrize("k,N,dtype,n,variant", [
+    (8, 16, torch.bfloat16, 20001, "plain"), (8, 16, torch.bfloat16, 20001, "fp32"),
+    (8, 64, torch.bfloat16, 330007, "strided"), (4, 256, torch.bfloat16, 60011, "strided"),
+    (4, 256, torch.float16, 60011, "fp32"), (4, 64, torch.float16, 30011, "plain"),
+    (4, 64, torch.bfloat16, 30011, "fp32"), (4, 16, torch.bfloat16, 10013, "strided"),
+    (4, 16, torch.float16, 10013, "plain"), (2, 256, torch.bfloat16, 70001, "fp32"),
+    (2, 256, torch.float16, 70001, "plain"), (2, 64, torch.float16, 50021, "strided"),
+    (2, 64, torch.bfloat16, 50021, "fp32"), (2, 16, torch.bfloat16, 30011, "plain"),
+    (2, 16, torch.float16, 30011, "strided")])
+def test_encode_tile_kernels_match_few_rows(k, N, dtype, n, variant, device):
     """The specialised codes' tile kernels take over from the general
     matrix-core encoder above a number of rows: one call over many rows gives
     the bytes of calls over few, for rows that fill and overflow the tile
-    kernels' near-tie queues (blocks at the midpoints of two codewords, rows
-    whose float32 sum of squares leaves its range), zero rows and ordinary
-    ones, and a sample of them is the oracle's."""
+    kernels' near-tie queues (blocks at the midpoints of a codeword and its
+    nearest neighbour, rows whose float32 sum of squares leaves its range),
+    zero rows and ordinary ones, dense and strided rows, codebooks with and
+    without ("fp32") exact binary16 entries; the special rows and a sample of
+    the others are the oracle's."""
     d = 64
     R = oracle_rotation(d)
-    C = quick_codebook(d, k, N).astype(np.float16).astype(np.float32)
+    C = quick_codebook(d, k, N)
+    if variant != "fp32":
+        C = C.astype(np.float16).astype(np.float32)
     Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
     g = torch.Generator().manual_seed(n)
     x = torch.randn(n, d, generator=g) * torch.exp(torch.randn(n, 1, generator=g))
-    rng = np.random.default_rng(n)
-    mid = 0.5 * (C[rng.integers(0, N, (512, d // k))] + C[rng.integers(0, N, (512, d // k))])
-    x[1000:1512] = torch.from_numpy(mid.reshape(512, d).astype(np.float32) @ R * 3.0)
+    mid, close = _midpoint_rows(np.random.default_rng(n), 1024, R, C, dtype)
+    # (ordinary rows: 0.05 to 0.4 % of the blocks; k = 2, N = 256 0.06 %)
+    assert close >= 1024 * (d // k) * 0.005, close
+    x[1000:2024] = mid.float()
     big = 2e38 if dtype == torch.bfloat16 else 6e4
     x[64:80] *= big / x[64:80].abs().max()            # 16 rows of one tile out of range
     x[4000:9000:129] *= 2.0 ** -60 if dtype == torch.bfloat16 else 2.0 ** -14
     x[96:128] = 0
     x[5000] = 0
     x = x.to(dtype)
-    xd = x.to(device)
-    _say(f"[edge] tile kernels against few rows k={k} N={N} {dtype} n={n}")
+    if variant == "strided":
+        xd = torch.empty(n, 2 * d, dtype=dtype, device=device)[:, :d]
+        xd.copy_(x)
+    else:
+        xd = x.to(device)
+    _say(f"[edge] tile kernels against few rows k={k} N={N} {dtype} n={n} {variant}: {close} blocks near ties")
     p, nrm = fq.encode(xd, k, N, Rd, Cd)
     few = [fq.encode(c, k, N, Rd, Cd) for c in xd.split(4096)]
     torch.cuda.synchronize()
     assert torch.equal(nrm, torch.cat([f[1] for f in few]))
     pf = torch.cat([f[0] for f in few])
     assert torch.equal(p, pf), f"{int((p != pf).any(1).sum())} rows differ"
-    some = torch.cat([torch.arange(60, 132), torch.arange(1000, 1100), torch.arange(4000, 9000, 129),
+    some = torch.cat([torch.arange(60, 132), torch.arange(1000, 2024), torch.arange(4000, 9000, 129),
                       torch.arange(n - 40, n)])
     gh.check_encode(gh.host_f64(x[some]), R, C, N, p[some.to(device)], nrm[some.to(device)])
 
@@ -624,19 +695,23 @@ def test_decode_out_of_range_ids_give_nan(k, N, device):
     assert torch.isfinite(out[[0, 1, 4]]).all()
 
 
-@pytest.mark.parametrize("T,T_stride,N,fp16_cb", [(0, 16, 64, False), (1, 8, 64, False),
-                                                   (65, 80, 64, False), (1000, 1100, 64, False),
-                                                   (70, 73, 16, False), (700, 701, 16, True),
-                                                   (2047, 2048, 64, True), (33, 33, 16, True)])
-def test_attention_token_counts(T, T_stride, N, fp16_cb, device):
+@pytest.mark.parametrize("T,T_stride,N,fp16_cb,n_g", [
+    (0, 16, 64, False, 3), (1, 8, 64, False, 3), (65, 80, 64, False, 3), (1000, 1100, 64, False, 3),
+    (70, 73, 16, False, 3), (700, 701, 16, True, 3), (2047, 2048, 64, True, 3), (33, 33, 16, True, 3),
+    # N = 16 goes to the 4-bit kernel from 16 groups on: strides that its 16-byte
+    # copies take and odd ones, codebooks with and without residuals
+    (0, 16, 16, False, 17), (1, 8, 16, True, 16), (33, 33, 16, True, 17), (63, 64, 16, False, 16),
+    (70, 73, 16, False, 17), (130, 144, 16, False, 40), (700, 701, 16, True, 17), (700, 704, 16, True, 17),
+    (700, 720, 16, False, 19), (2047, 2048, 16, True, 17), (1999, 2048, 16, False, 32)])
+def test_attention_token_counts(T, T_stride, N, fp16_cb, n_g, device):
     """T = 0 writes zeros; T = 1 returns the single value; ragged tails and
-    T_stride > T (bytes beyond T are junk and must be ignored)."""
+    T_stride > T (bytes beyond T are junk and must be ignored), in the
+    matrix-core kernel of all codes and in the 4-bit code's own."""
     d, k, G = 64, 8, 8
     R, C = oracle_rotation(d), quick_codebook(d, k, N)
     if fp16_cb:  # a codebook whose entries are exactly representable in binary16
         C = C.astype(np.float16).astype(np.float32)
     Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
-    n_g = 3
     rng = np.random.default_rng(T)
     P = occ.payload_bytes(d, k, N)
     idx_k = rng.integers(0, N, (n_g, T_stride, d // k))
@@ -647,7 +722,7 @@ def test_attention_token_counts(T, T_stride, N, fp16_cb, device):
     vp = occ.pack(idx_v.reshape(-1, d // k), N).reshape(n_g, T_stride, P)
     q = rng.standard_normal((n_g, G, d)).astype(np.float32)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(device)
-    _say(f"[edge] attention T={T} T_stride={T_stride} N={N} fp16 codebook={fp16_cb}")
+    _say(f"[edge] attention T={T} T_stride={T_stride} N={N} fp16 codebook={fp16_cb} n_g={n_g}")
     o = fq.attn_decode(dev(q), dev(kp), dev(occ.fp16_bits(hk).view(np.int16)), dev(vp),
                        dev(occ.fp16_bits(hv).view(np.int16)), T, k, N, Rd, Cd).cpu().numpy()
     if T == 0:
@@ -693,13 +768,15 @@ def test_attention_many_short_groups(N, n_g, T, device):
 def test_attention_workspace_reuse_across_shapes(device):
     """One workspace serves a sequence of calls of different shapes and
     kernels (the two-launch and three-launch forms of the 4-bit kernel, the
-    6-bit kernel, the k = 4 kernel): whatever an earlier call left in it,
-    every result matches the oracle."""
+    matrix-core kernel of the other codes with few and with many groups, the
+    general kernels): whatever an earlier call left in it, every result
+    matches the oracle."""
     d, G = 64, 8
     R = oracle_rotation(d)
     Rd = torch.from_numpy(R.copy()).to(device)
-    calls = [(8, 16, 5, 5000), (8, 16, 1100, 70), (8, 64, 4, 3000), (4, 256, 6, 700),
-             (8, 16, 3, 7777), (8, 16, 5, 5000)]
+    calls = [(8, 16, 24, 5000), (8, 16, 1100, 70), (8, 64, 4, 3000), (4, 256, 6, 700),
+             (8, 16, 17, 777), (8, 16, 5, 5000), (4, 256, 1100, 70), (1, 16, 3, 300),
+             (8, 16, 3, 7777), (8, 16, 24, 5000)]
     books = {}
     need = max(fq.attn_workspace_bytes(n_g, G, T, d, k, N) for k, N, n_g, T in calls)
     ws = torch.full((need,), 0xA5, dtype=torch.uint8, device=device)  # junk, not zeros
@@ -719,12 +796,13 @@ def test_attention_workspace_reuse_across_shapes(device):
         gh.check_attention(o, ref)
 
 
-@pytest.mark.parametrize("N", [16, 64])
-def test_attention_huge_query_small_keys(N, device):
-    """Rotated query entries far beyond binary16 range (the matrix-core path
-    rescales them by a power of two) against tiny key norms, so the logits
-    stay moderate and the softmax is well conditioned."""
-    d, k, G, T, n_g = 64, 8, 8, 700, 3
+@pytest.mark.parametrize("N,n_g", [(16, 3), (64, 3), (16, 17), (16, 700)])
+def test_attention_huge_query_small_keys(N, n_g, device):
+    """Rotated query entries far beyond binary16 range (the matrix-core paths
+    rescale them by a power of two; N = 16 from 16 groups on is the 4-bit
+    kernel, many groups its separate query preparation) against tiny key
+    norms, so the logits stay moderate and the softmax is well conditioned."""
+    d, k, G, T = 64, 8, 8, 700 if n_g < 100 else 65
     R = oracle_rotation(d)
     C = quick_codebook(d, k, N).astype(np.float16).astype(np.float32)
     Rd, Cd = torch.from_numpy(R.copy()).to(device), torch.from_numpy(C.copy()).to(device)
@@ -738,7 +816,7 @@ def test_attention_huge_query_small_keys(N, device):
     vp = occ.pack(idx_v, N).reshape(n_g, T, P)
     q = (rng.standard_normal((n_g, G, d)) * 3e5).astype(np.float32)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(device)
-    _say(f"[edge] attention huge query N={N}")
+    _say(f"[edge] attention huge query N={N} n_g={n_g}")
     o = fq.attn_decode(dev(q), dev(kp), dev(occ.fp16_bits(hk).view(np.int16).reshape(n_g, T)),
                        dev(vp), dev(occ.fp16_bits(hv).view(np.int16).reshape(n_g, T)), T, k, N,
                        Rd, Cd).cpu().numpy()
@@ -792,6 +870,9 @@ def test_attention_k4_shapes(d, k, N, G, T, T_stride, fp16_cb, qmul, device):
 @pytest.mark.parametrize("d,k,N,G,n_g,T,T_stride,fp16_cb", [
     (64, 8, 64, 8, 2, 1024, 1024, True), (64, 8, 64, 8, 2, 1025, 1030, True),
     (64, 8, 64, 3, 300, 65, 67, False), (64, 8, 16, 4, 1, 33, 33, True),
+    (64, 8, 32, 8, 3, 700, 701, False), (64, 8, 32, 1, 2, 31, 31, True),
+    (64, 8, 128, 4, 3, 257, 261, True), (64, 16, 128, 8, 2, 333, 335, False),
+    (64, 16, 128, 1, 40, 64, 65, True),
     (64, 8, 256, 8, 5, 257, 257, True), (64, 8, 1024, 1, 2, 31, 40, False),
     (64, 8, 4096, 5, 2, 1500, 1501, True), (64, 16, 256, 2, 3, 700, 703, True),
     (64, 16, 2048, 8, 1, 129, 129, False), (64, 4, 1024, 7, 2, 1300, 1300, False),
