@@ -480,17 +480,15 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
   f4 acc[VM];
   float m_run = -INFINITY, l_run = 0.0f, qsg = 1.0f;
   // Scale of the weights p nu_V: a binary16 part holds 11 bits only above
-  // 2^-14, and value norms go down to 2^-24.  wsc starts at 2^14 in every group
-  // and drops to 1 at the first norm of 2 or more (wmask: the exponent bit that
-  // says so, in both halves of a word; 0 from then on); avs undoes it.
-  _Float16 wsc = (_Float16)kVs;
-  uint32_t wmask = 0x40004000u;
-  float avs = ci / kVs;
+  // 2^-14, and value norms go down to 2^-24.  In every group it is 2^14 up to
+  // the first unit with a norm of 2 or more, then 1.
+  bool small = true, drop = false;  // drop: at the present unit
   int64_t cur_group = -1;
 
   auto flush = [&](auto* r) {
     // rows h and h + 8 (high parts of the weights, rest times 2^11) sit in
     // lanes l and l ^ 32
+    const float avs = small ? ci / kVs : ci;  // undoes the scales
     float l = l_run;
     l = xsum(l, 8);
     l = xsum(l, 16);
@@ -555,10 +553,9 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
       for (int e = 0; e < 4; ++e) t4[e] = (ts + e < T) ? t4[e] : -INFINITY;
     }
     const float tmx = fmaxf(fmaxf(t4[0], t4[1]), fmaxf(t4[2], t4[3]));
-    const uint32_t big = (b.nv[0] | b.nv[1]) & wmask;
-    // a token beats the running maximum or a value norm its range, or (not a
-    // number) no finite score has come yet and an infinite key norm scores -inf
-    if (__any(!(tmx <= 0.0f) || big != 0)) {
+    // a token beats the running maximum, or (not a number) no finite score has
+    // come yet and an infinite key norm scores -inf
+    if (__any(!(tmx <= 0.0f)) || drop) {
       // the maximum first, then every score against it in one fma (a score
       // of 100 rounded by itself would move its weight by 4e-6)
       const bool first = m_run == -INFINITY;  // nothing accumulated yet for this group
@@ -577,24 +574,19 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
       const float m_new = first ? mh : m_run + fmaxf(mh, 0.0f);
       const float delta = first ? INFINITY : m_new - m_run;
       m_run = m_new;
+      const float m_sub = m_run == -INFINITY ? 0.0f : m_run;  // (scores of -inf keep weight 0)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const h2 nk2 = __builtin_bit_cast(h2, b.nk[e >> 1]);
-        const float nk = (float)nk2[e & 1], t = fmaf(f4s[e], nk, -m_run);
-        t4[e] = (full || ts + e < T) && f4s[e] * nk != -INFINITY ? t : -INFINITY;  // (weight 0)
+        const float t = fmaf(f4s[e], (float)nk2[e & 1], -m_sub);
+        t4[e] = (full || ts + e < T) ? t : -INFINITY;
       }
       const float alpha = __builtin_amdgcn_exp2f(-delta * qsg);
       l_run *= alpha;
-      float beta = 1.0f;
-      if (__any(big != 0)) {
-        beta = 1.0f / kVs;
-        wsc = (_Float16)1.0f;
-        wmask = 0;
-        avs = ci;
-      }
+      const float beta = drop ? alpha * (1.0f / kVs) : alpha;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {  // accumulator row 4 g16 + e belongs to head (4 g16 + e) & 7
-        const float ar = __shfl(alpha, (4 * g16 + e) & 7, 64) * beta;
+        const float ar = __shfl(beta, (4 * g16 + e) & 7, 64);
 #pragma unroll
         for (int mu = 0; mu < VM; ++mu) acc[mu][e] *= ar;
       }
@@ -612,7 +604,7 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
     u4v au;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const h2 nv2 = __builtin_bit_cast(h2, b.nv[i]) * h2{wsc, wsc};  // (exact: norms below 2, or times 1)
+      const h2 nv2 = __builtin_bit_cast(h2, b.nv[i]);
       const float w0 = p[2 * i] * (float)nv2[0], w1 = p[2 * i + 1] * (float)nv2[1];
       uint32_t uh = __builtin_bit_cast(uint32_t, h2{(_Float16)w0, (_Float16)w1});
       asm("" : "+v"(uh));  // the rest is taken from these bits (not from a conversion fused anew)
@@ -667,9 +659,17 @@ __global__ __launch_bounds__(64 * whole_waves(D)) void main_kernel(
         for (int mu = 0; mu < VM; ++mu) acc[mu] = f4{0, 0, 0, 0};
         m_run = -INFINITY;
         l_run = 0.0f;
-        wsc = (_Float16)kVs;
-        wmask = 0x40004000u;
-        avs = ci / kVs;
+        small = true;
+      }
+      drop = false;
+      if (small) {  // (uniform)
+        drop = __any(((cur.nv[0] | cur.nv[1]) & 0x40004000u) != 0);  // an exponent of 1 or more
+        small = !drop;
+        if (small) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i)  // (exact)
+            cur.nv[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, cur.nv[i]) * (_Float16)kVs);
+        }
       }
       int64_t ngrp = grp;
       int nstep = step + 1;
