@@ -745,11 +745,13 @@ def _random_attention_inputs(rng, n_g, T, d, k, N, G, kscale=30.0):
     return q, kp, hk, vp, hv
 
 
-@pytest.mark.parametrize("N,n_g,T", [(16, 1100, 70), (16, 600, 300), (64, 1100, 70)])
+@pytest.mark.parametrize("N,n_g,T", [(16, 1100, 70), (16, 600, 300), (64, 1100, 70), (16, 1279, 33),
+                                     (16, 1280, 33), (16, 1281, 200), (16, 2600, 9)])
 def test_attention_many_short_groups(N, n_g, T, device):
     """Many short groups: each workgroup of the sub-one-bit kernels meets
     more groups than it keeps query operands for, which takes the 4-bit
-    kernel's three-launch form (a separate query preparation kernel)."""
+    kernel's three-launch form (a separate query preparation kernel), with
+    two merge blocks per group and, from 1280 groups on, one."""
     d, k, G = 64, 8, 8
     R = oracle_rotation(d)
     C = quick_codebook(d, k, N).astype(np.float16).astype(np.float32)
